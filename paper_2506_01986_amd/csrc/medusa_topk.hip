@@ -4,12 +4,14 @@
 // top-k tokens populate level i+1 of the candidate tree (Eq. 2); a node's token
 // depends only on its depth and rank.
 //
-// head_logits_bf16: z[b][i][v] = sum_c W[i][v][c] * h[b][c].  The weight stream
-// (l * vocab * hidden bf16, 2.1 GB for a 70B-shaped model) is the largest read of
-// the step and is HBM-bound for any batch, so each wave streams 64 vocabulary rows
-// with 16-byte loads and contracts them against up to 16 hidden states on the
-// 16x16x32 bf16 matrix cores (batch padded to 16: the padding costs matrix-core
-// time that is far below the load time).
+// z[b][i][v] = sum_c W[i][v][c] * h[b][c].  The weight stream (l * vocab * hidden
+// bf16, 2.1 GB for a 70B-shaped model) is the largest read of the step and is
+// HBM-bound for any batch of a verify step, so waves stream 64 vocabulary rows
+// each with 16-byte loads and contract them on the 16x16x32 bf16 matrix cores
+// (batch padded to 16s: the padding costs matrix-core time that is far below
+// the load time).  Packed heads: packed_gemm; row-major ones: head_logits_bf16.
+#include <type_traits>
+
 #include "device.h"
 #include "internal.h"
 
@@ -112,12 +114,6 @@ __global__ __launch_bounds__(kWaves * 64) void head_logits_bf16(
   }
 }
 
-// Packed heads (see specmemo_pack_heads): wave (head, G) streams its row
-// group's nS * 4 KB contiguously, one 1 KB operand tile per load instruction,
-// and contracts each tile against the 16 hidden states of its batch tile.
-constexpr int kPackedUnroll = 4;   // k steps (4 KB each) issued before their MFMAs
-constexpr int kHidChunk = 16;      // k steps of hidden states staged in LDS at a time (two batch tiles)
-
 // Weights are read once per step: nontemporal loads keep them from displacing
 // the hidden states and logits in the caches.
 typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
@@ -125,252 +121,233 @@ __device__ __forceinline__ uint4 ld16_stream(const uint4 *p) {
   return __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(p)));
 }
 
-// gmax non-null: each (batch row, head) row also gets the maximum of every
-// 64-row group, [B][n_heads][nG], from which the top-k pass finds the groups
-// that can hold a top-k value.
-template <int NB>
-__global__ __launch_bounds__(kWaves * 64) void head_logits_packed(
-    const uint16_t *__restrict__ h, int64_t h_head_stride, const uint4 *__restrict__ Wp, float *__restrict__ z,
-    int B, int hidden, int vocab, int n_heads, int nG, int nS, float *__restrict__ gmax) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+// Packed weights (see specmemo_pack_heads) against up to 16 NB hidden states:
+// head_logits with EPI = 0, residual blocks with EPI = 1.
+//
+// Bound by the weight stream (HBM) up to 128 hidden states, so the weights are
+// read once for all of them: a wave keeps the accumulators of one 64-row group
+// x 16 NB states in registers and streams the group's 1 KB operand tiles.
+// 4 heads x 32000 x 8192: 10 states 307 us, 120 states 338 us (6.4 TB/s; 1345 us
+// when 32 states were the most that shared a stream).
+//
+// KS waves share a row group and split its k steps in contiguous ranges, whose
+// partial sums meet in LDS: see launch_packed_nb for when.
+//
+// Weights: PRE k steps (4 KB each) in flight per wave, a step's registers
+// refilled right after its products; BURST (one batch tile): eight steps at a
+// time, refilled together, the states read at their use.  States of one batch
+// tile: each wave loads its own beside the weights.  Of more: the block's waves share them
+// through LDS in chunks of KC k steps per range, two buffers; a chunk is
+// fetched to registers two chunks ahead and stored one ahead, and the barrier
+// between chunks is bare, because __syncthreads() would wait for the weights
+// in flight.  LDS entry of (row r, 8-column part c) of a 1 KB piece is
+// 4 r + (c ^ state_slot_swz(r)): a wave's 16-byte writes (four lanes a row, as they
+// are coalesced) and reads (16 rows at one part) are both free of bank
+// conflicts.
+//
+// EPI = 0, gmax non-null: each (batch row, head) row also gets the maximum of
+// every 64-row group, [B][n_heads][nG], from which the top-k pass finds the
+// groups that can hold a top-k value.
+__device__ __forceinline__ int state_slot_swz(int r) { return ((r >> 1) ^ (r >> 2)) & 3; }
+
+template <int NW, int NB, int KS, int KC, int EPI, bool BURST = false>
+__global__ __launch_bounds__(64 * NW, 8 / NW) void packed_gemm(
+    const uint16_t *__restrict__ h, int64_t h_head_stride, const uint4 *__restrict__ Wp,
+    const uint16_t *__restrict__ bias, float *__restrict__ z, uint16_t *__restrict__ hout, int B, int hidden, int rows,
+    int n_heads, int nG, int nS, float *__restrict__ gmax) {
+  constexpr int PRE = BURST ? 8 : 4;             // k steps in flight per wave
+  constexpr bool kShare = NB > 1;                // states through LDS
+  static_assert(PRE % KC == 0 && NW % KS == 0 && (!kShare || (NB * KS * KC) % NW == 0), "whole chunks and pieces");
+  constexpr int RG = NW / KS;                    // row groups per block
+  constexpr int kPer = kShare ? NB * KS * KC / NW : 1;   // 16-byte pieces of a chunk per thread
+  constexpr int kBuf = kShare ? KS * KC * NB * 64 : 0;        // entries of a states buffer
+  constexpr int kRed = KS > 1 ? NW * 4 * 64 : 0; // a batch tile of every wave, for the ranges' sums
+  __shared__ u32x4_t hsh[2 * kBuf > kRed ? 2 * kBuf : kRed > 0 ? kRed : 1];
+  // the wave's number, made uniform for the compiler: its bases then stay in scalar registers
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int head = blockIdx.y, b0 = blockIdx.z * 16 * NB;
-  const int G = blockIdx.x * kWaves + wave;
+  const int G = blockIdx.x * RG + wave / KS, sl = wave % KS;
   const bool active = G < nG;
-  const int kq = lane >> 4;
-  const uint4 *wp = Wp + (int64_t)(head * (int64_t)nG + (active ? G : 0)) * nS * 4 * 64 + lane;
+  const int r16 = lane & 15, kq = lane >> 4;
+  const int nF = hidden >> 5;                    // whole k steps; a rest of hidden % 32 columns follows the loop
+  const int len = (nF + KS - 1) / KS;            // k steps of a range (the last ranges may hold fewer)
+  const int s_begin = sl * len, n_mine = max(0, min(nF - s_begin, len));
+  // pipelined steps: whole groups of PRE that every range has
+  const int n_main = max(0, nF - (KS - 1) * len) / PRE * PRE;
+  const uint4 *wp = Wp + ((int64_t)(head * (int64_t)nG + (active ? G : 0)) * nS + s_begin) * 4 * 64;
+  const uint16_t *hbase = h + head * h_head_stride;
+
   f32x4 acc[NB][4];
 #pragma unroll
   for (int n = 0; n < NB; ++n)
 #pragma unroll
     for (int t = 0; t < 4; ++t) acc[n][t] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  if constexpr (NB == 1) {
-    // One batch tile: each wave reads its hidden-state fragments itself.
-    if (!active) return;
-    bool bvalid[NB];
-    const uint16_t *hp[NB];
+  u32x4_t hreg[kPer];
+  uint32_t hoff[kPer];                           // this thread's bytes of the pieces, from row b0
 #pragma unroll
-    for (int n = 0; n < NB; ++n) {
-      const int b = b0 + 16 * n + (lane & 15);
-      bvalid[n] = b < B;
-      hp[n] = h + head * h_head_stride + (int64_t)(bvalid[n] ? b : 0) * hidden + kq * 8;
-    }
-    auto step = [&](const uint4 (&a)[4], int s) {
-      const int k = 32 * s + 8 * kq;
-#pragma unroll
-      for (int n = 0; n < NB; ++n) {
-        const bf16x8 bv = __builtin_bit_cast(bf16x8, ld16_or_zero(bvalid[n] && k < hidden, hp[n] + 32 * s));
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-          acc[n][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[t]), bv, acc[n][t], 0, 0, 0);
-      }
-    };
-    int s = 0;
-    for (; s + kPackedUnroll <= nS; s += kPackedUnroll) {
-      uint4 a[kPackedUnroll][4];
-#pragma unroll
-      for (int u = 0; u < kPackedUnroll; ++u)
-#pragma unroll
-        for (int t = 0; t < 4; ++t) a[u][t] = ld16_stream(wp + ((s + u) * 4 + t) * 64);
-#pragma unroll
-      for (int u = 0; u < kPackedUnroll; ++u) step(a[u], s + u);
-    }
-    for (; s < nS; ++s) {
-      uint4 a[4];
-#pragma unroll
-      for (int t = 0; t < 4; ++t) a[t] = ld16_stream(wp + (s * 4 + t) * 64);
-      step(a, s);
-    }
-  } else {
-    // Two batch tiles: the second hidden-state gather per k step made the
-    // vector cache the bottleneck, so the block's waves share their hidden
-    // states through LDS: chunks of kHidChunk k steps (two buffers) in the B
-    // operand's lane order, one 1 KB piece per (step, batch tile), read with
-    // one conflict-free 16-byte LDS read per step and tile.  Entry e of a
-    // piece holds row e % 16, columns 32 (step) + 8 (e / 16) .. +8; rows past
-    // B, columns past hidden and steps past nS are zero.  Waves past the last
-    // row group still stage hidden states and meet the barriers.
-    constexpr int kPieces = kHidChunk * NB * 64;
-    constexpr int kPer = kPieces / (kWaves * 64);
-    __shared__ uint4 hsh[2][kPieces];
-    const uint16_t *hbase = h + head * h_head_stride;
-    uint4 hreg[kPer];
-    auto hfetch = [&](int c) {
-#pragma unroll
-      for (int i = 0; i < kPer; ++i) {
-        const int q = tid + i * kWaves * 64;
-        const int kk = q & 3, row = (q >> 2) & 15, pn = q >> 6;
-        const int n = pn % NB, sl = pn / NB;
-        const int st = c * kHidChunk + sl, b = b0 + 16 * n + row, k = 32 * st + 8 * kk;
-        const bool ok = b < B && k < hidden && st < nS;
-        const uint4 v = *reinterpret_cast<const uint4 *>(hbase + (int64_t)(b < B ? b : 0) * hidden + min(k, hidden - 8));
-        hreg[i] = ok ? v : uint4{0u, 0u, 0u, 0u};
-      }
-    };
-    auto hstore = [&](int buf) {
-#pragma unroll
-      for (int i = 0; i < kPer; ++i) {
-        const int q = tid + i * kWaves * 64;
-        hsh[buf][(q >> 6) * 64 + (q & 3) * 16 + ((q >> 2) & 15)] = hreg[i];
-      }
-    };
-    auto step = [&](const uint4 (&a)[4], const uint4 *hb, int sl) {
-#pragma unroll
-      for (int n = 0; n < NB; ++n) {
-        const bf16x8 bv = __builtin_bit_cast(bf16x8, hb[(sl * NB + n) * 64 + lane]);
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-          acc[n][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[t]), bv, acc[n][t], 0, 0, 0);
-      }
-    };
-    const int nch = (nS + kHidChunk - 1) / kHidChunk;
-    hfetch(0);
-    hstore(0);
-    __syncthreads();
-    for (int c = 0; c < nch; ++c) {
-      if (c + 1 < nch) hfetch(c + 1);
-      const uint4 *hb = hsh[c & 1];
-      const int s0 = c * kHidChunk, s1 = min(nS, s0 + kHidChunk);
-      if (active) {
-        int s = s0;
-        for (; s + kPackedUnroll <= s1; s += kPackedUnroll) {
-          uint4 a[kPackedUnroll][4];
-#pragma unroll
-          for (int u = 0; u < kPackedUnroll; ++u)
-#pragma unroll
-            for (int t = 0; t < 4; ++t) a[u][t] = ld16_stream(wp + ((s + u) * 4 + t) * 64);
-#pragma unroll
-          for (int u = 0; u < kPackedUnroll; ++u) step(a[u], hb, s - s0 + u);
-        }
-        for (; s < s1; ++s) {
-          uint4 a[4];
-#pragma unroll
-          for (int t = 0; t < 4; ++t) a[t] = ld16_stream(wp + (s * 4 + t) * 64);
-          step(a, hb, s - s0);
-        }
-      }
-      if (c + 1 < nch) hstore((c + 1) & 1);
-      __syncthreads();
-    }
-    if (!active) return;
+  for (int i = 0; i < kPer; ++i) {
+    const int n = (i * NW + wave) % NB;        // piece NW i + wave: batch tile, then step of the chunk, then range
+    hoff[i] = (uint32_t)min(16 * n + (lane >> 2), B - 1 - b0) * (uint32_t)(2 * hidden) + 16u * (lane & 3);
   }
-
-  // C layout: lane holds column (batch) lane&15, rows 4*(lane>>4) + 0..3 of each tile.
+  const uint8_t *hb0 = reinterpret_cast<const uint8_t *>(hbase + (int64_t)b0 * hidden);
+  auto hfetch = [&](int c) {   // rows past B repeat the last one, chunks past the end the last step: neither is used
 #pragma unroll
-  for (int n = 0; n < NB; ++n) {
-    const int b = b0 + 16 * n + (lane & 15);
-    float m = -INFINITY;
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const int row = 64 * G + t * 16 + 4 * kq;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) m = row + j < vocab ? fmaxf(m, acc[n][t][j]) : m;
-    }
-    if (gmax) {   // the column's four lanes: l, l ^ 16, l ^ 32, l ^ 48
-      m = fmaxf(m, __shfl_xor(m, 16));
-      m = fmaxf(m, __shfl_xor(m, 32));
-    }
-    if (b >= B) continue;
-    float *zr = z + ((int64_t)b * n_heads + head) * vocab;
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const int row = 64 * G + t * 16 + 4 * kq;
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        if (row + j < vocab) zr[row + j] = acc[n][t][j];
-    }
-    if (gmax && kq == 0) gmax[((int64_t)b * n_heads + head) * nG + G] = m;
-  }
-}
-
-// Medusa residual blocks on packed weights: out[head][b][row] =
-// h[b][row] + SiLU(sum_k W1[head][row][k] h[b][k] + b1[head][row]), in bf16.
-// A block's four waves share one 64-row group and split its k steps in four
-// contiguous ranges (hidden x hidden weights have 64x fewer row groups per
-// head than a vocabulary projection, so one wave per row group would leave
-// most compute units idle); the partial sums meet in LDS.
-constexpr int kResSplit = 4;
-
-template <int NB>
-__global__ __launch_bounds__(kResSplit * 64) void resblock_packed(
-    const uint16_t *__restrict__ h, const uint4 *__restrict__ Wp, const uint16_t *__restrict__ bias,
-    uint16_t *__restrict__ hout, int B, int hidden, int nG, int nS) {
-  __shared__ f32x4 red[kResSplit - 1][NB][4][64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int G = blockIdx.x, head = blockIdx.y, b0 = blockIdx.z * 16 * NB;
-  const int kq = lane >> 4;
-  const uint4 *wp = Wp + (int64_t)(head * nG + G) * nS * 4 * 64 + lane;
-  bool bvalid[NB];
-  const uint16_t *hp[NB];
-#pragma unroll
-  for (int n = 0; n < NB; ++n) {
-    const int b = b0 + 16 * n + (lane & 15);
-    bvalid[n] = b < B;
-    hp[n] = h + (int64_t)(bvalid[n] ? b : 0) * hidden + kq * 8;
-  }
-  f32x4 acc[NB][4];
-#pragma unroll
-  for (int n = 0; n < NB; ++n)
-#pragma unroll
-    for (int t = 0; t < 4; ++t) acc[n][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-  auto step = [&](const uint4 (&a)[4], int s) {
-    const int k = 32 * s + 8 * kq;
-#pragma unroll
-    for (int n = 0; n < NB; ++n) {
-      const bf16x8 bv = __builtin_bit_cast(bf16x8, ld16_or_zero(bvalid[n] && k < hidden, hp[n] + 32 * s));
-#pragma unroll
-      for (int t = 0; t < 4; ++t)
-        acc[n][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[t]), bv, acc[n][t], 0, 0, 0);
+    for (int i = 0; i < kPer; ++i) {
+      const int r = (i * NW + wave) / NB;
+      const int st = min((r / KC) * len + c * KC + r % KC, nF - 1);
+      hreg[i] = *reinterpret_cast<const u32x4_t *>(hb0 + 64 * (int64_t)st + hoff[i]);
     }
   };
-  const int s_end = (wave + 1) * nS / kResSplit;
-  int s = wave * nS / kResSplit;
-  for (; s + kPackedUnroll <= s_end; s += kPackedUnroll) {
-    uint4 a[kPackedUnroll][4];
+  const int wr = (lane & ~3) + ((lane & 3) ^ state_slot_swz(lane >> 2));
+  auto hstore = [&](int buf) {
 #pragma unroll
-    for (int u = 0; u < kPackedUnroll; ++u)
+    for (int i = 0; i < kPer; ++i) hsh[buf * kBuf + (i * NW + wave) * 64 + wr] = hreg[i];
+  };
+  const int rd = 4 * r16 + (kq ^ state_slot_swz(r16));
+
+  auto contract = [&](const uint4 (&at)[4], const bf16x8 &bv, int n) {
 #pragma unroll
-      for (int t = 0; t < 4; ++t) a[u][t] = ld16_stream(wp + ((s + u) * 4 + t) * 64);
+    for (int t = 0; t < 4; ++t)
+      acc[n][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, at[t]), bv, acc[n][t], 0, 0, 0);
+  };
+  if (n_main > 0) {
+    // No branch between the loads in flight: one that may be skipped makes the
+    // compiler wait for all of them.
+    uint4 a[PRE][4];
+    u32x4_t own[kShare ? 1 : PRE];               // one batch tile: the wave's own states, loaded with the weights
+    const uint16_t *ho = hbase + (int64_t)min(b0 + r16, B - 1) * hidden + 32 * s_begin + 8 * kq;
+    auto fetch = [&](int s, int u) {
+      if constexpr (!kShare && !BURST) own[u] = *reinterpret_cast<const u32x4_t *>(ho + 32 * s);
+      const uint4 *wn = wp + (int64_t)s * 4 * 64;
 #pragma unroll
-    for (int u = 0; u < kPackedUnroll; ++u) step(a[u], s + u);
+      for (int t = 0; t < 4; ++t) a[u][t] = ld16_stream(wn + t * 64 + lane);
+    };
+    auto group = [&](int t0, auto more) {        // PRE steps; `more`: each then fetches the step PRE further on
+#pragma unroll
+      for (int u = 0; u < PRE; ++u) {
+        if constexpr (kShare) {
+          const int c = (t0 + u) / KC;           // chunk of this step
+          if (u % KC == 0) {
+            hstore((c + 1) & 1);
+            hfetch(c + 2);
+          }
+          const u32x4_t *hb = &hsh[(c & 1) * kBuf + ((sl * KC + u % KC) * NB) * 64 + rd];
+#pragma unroll
+          for (int n = 0; n < NB; ++n) contract(a[u], __builtin_bit_cast(bf16x8, hb[n * 64]), n);
+        } else if constexpr (BURST) {
+          contract(a[u], __builtin_bit_cast(bf16x8, ld16_or_zero(b0 + r16 < B, ho + 32 * (t0 + u))), 0);
+        } else {
+          contract(a[u], __builtin_bit_cast(bf16x8, own[u]), 0);
+        }
+        if constexpr (!BURST) {
+          if constexpr (decltype(more)::value) fetch(t0 + u + PRE, u);
+          __builtin_amdgcn_sched_barrier(0);     // the loads stay here: their distance is the prefetch
+        }
+        if (kShare && u % KC == KC - 1) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      }
+      if constexpr (BURST && decltype(more)::value)
+#pragma unroll
+        for (int u = 0; u < PRE; ++u) fetch(t0 + PRE + u, u);
+    };
+#pragma unroll
+    for (int u = 0; u < PRE; ++u) fetch(u, u);
+    if constexpr (kShare) {
+      hfetch(0);
+      hstore(0);
+      hfetch(1);
+      __syncthreads();
+    }
+    int t0 = 0;
+    for (; t0 + PRE < n_main; t0 += PRE) group(t0, std::true_type{});
+    group(t0, std::false_type{});
   }
-  for (; s < s_end; ++s) {
-    uint4 a[4];
+  // The range's last steps, and in the last range hidden % 32 columns more,
+  // four at a time: states straight from memory, zero past hidden.
+  const int n_all = n_mine + (sl == KS - 1 ? nS - nF : 0);
+  for (int s0 = n_main; s0 < n_all; s0 += 4) {
+    uint4 at[4][4];
 #pragma unroll
-    for (int t = 0; t < 4; ++t) a[t] = ld16_stream(wp + (s * 4 + t) * 64);
-    step(a, s);
+    for (int u = 0; u < 4; ++u) {
+      const int s = min(s0 + u, n_all - 1), st = s < n_mine ? s_begin + s : nF;
+#pragma unroll
+      for (int t = 0; t < 4; ++t) at[u][t] = ld16_stream(wp + ((int64_t)(st - s_begin) * 4 + t) * 64 + lane);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (s0 + u < n_all) {
+        const int k = 32 * (s0 + u < n_mine ? s_begin + s0 + u : nF) + 8 * kq;
+#pragma unroll
+        for (int n = 0; n < NB; ++n) {
+          const int b = b0 + 16 * n + r16;
+          const bool in = b < B && k < hidden;
+          contract(at[u], __builtin_bit_cast(bf16x8, ld16_or_zero(in, hbase + (int64_t)(in ? b : 0) * hidden + (in ? k : 0))), n);
+        }
+      }
   }
-  if (wave > 0) {
+  if constexpr (KS > 1) {                        // the ranges' sums, added in range order; one batch tile at a time
+    f32x4 *red = reinterpret_cast<f32x4 *>(hsh);
 #pragma unroll
-    for (int n = 0; n < NB; ++n)
+    for (int n = 0; n < NB; ++n) {
+      __syncthreads();
+      if (sl > 0)
 #pragma unroll
-      for (int t = 0; t < 4; ++t) red[wave - 1][n][t][lane] = acc[n][t];
+        for (int t = 0; t < 4; ++t) red[(wave * 4 + t) * 64 + lane] = acc[n][t];
+      __syncthreads();
+      if (sl == 0)
+#pragma unroll
+        for (int w = 1; w < KS; ++w)
+#pragma unroll
+          for (int t = 0; t < 4; ++t) acc[n][t] += red[((wave + w) * 4 + t) * 64 + lane];
+    }
+    if (sl > 0) return;
   }
-  __syncthreads();
-  if (wave > 0) return;
-#pragma unroll
-  for (int w = 0; w < kResSplit - 1; ++w)
-#pragma unroll
-    for (int n = 0; n < NB; ++n)
-#pragma unroll
-      for (int t = 0; t < 4; ++t) acc[n][t] += red[w][n][t][lane];
+  if (!active) return;
   // C layout: lane holds column (batch) lane&15, rows 4*(lane>>4) + 0..3 of each tile.
 #pragma unroll
   for (int n = 0; n < NB; ++n) {
-    const int b = b0 + 16 * n + (lane & 15);
-    if (b >= B) continue;
-    const uint16_t *hin = h + (int64_t)b * hidden;
-    const uint16_t *bh = bias + (int64_t)head * hidden;
-    uint16_t *o = hout + ((int64_t)head * B + b) * hidden;
+    const int b = b0 + 16 * n + r16;
+    if constexpr (EPI == 0) {
+      float m = -INFINITY;
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const int row = 64 * G + t * 16 + 4 * kq;
+      for (int t = 0; t < 4; ++t) {
+        const int row = 64 * G + t * 16 + 4 * kq;
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
-        if (row + j < hidden) {
-          const float y = acc[n][t][j] + bf16_to_f32(bh[row + j]);
-          o[row + j] = f32_to_bf16(bf16_to_f32(hin[row + j]) + y / (1.f + expf(-y)));
+        for (int j = 0; j < 4; ++j) m = row + j < rows ? fmaxf(m, acc[n][t][j]) : m;
+      }
+      if (gmax) {   // the column's four lanes: l, l ^ 16, l ^ 32, l ^ 48
+        m = fmaxf(m, __shfl_xor(m, 16));
+        m = fmaxf(m, __shfl_xor(m, 32));
+      }
+      if (b >= B) continue;
+      float *zr = z + ((int64_t)b * n_heads + head) * rows;
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const int row = 64 * G + t * 16 + 4 * kq;
+        if ((rows & 3) == 0) {                   // rows start 16-byte aligned: the lane's four are all in or all out
+          if (row < rows) *reinterpret_cast<f32x4 *>(zr + row) = acc[n][t];
+        } else {
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            if (row + j < rows) zr[row + j] = acc[n][t][j];
         }
+      }
+      if (gmax && kq == 0) gmax[((int64_t)b * n_heads + head) * nG + G] = m;
+    } else {
+      if (b >= B) continue;
+      const uint16_t *hin = h + (int64_t)b * hidden;
+      const uint16_t *bh = bias + (int64_t)head * hidden;
+      uint16_t *o = hout + ((int64_t)head * B + b) * hidden;
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const int row = 64 * G + t * 16 + 4 * kq;
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          if (row + j < hidden) {
+            const float y = acc[n][t][j] + bf16_to_f32(bh[row + j]);
+            o[row + j] = f32_to_bf16(bf16_to_f32(hin[row + j]) + y / (1.f + expf(-y)));
+          }
+      }
     }
   }
 }
@@ -676,16 +653,72 @@ __global__ __launch_bounds__(kTopkThreads) void topk_rows(TopkArgs a) {
 
 }  // namespace
 
+namespace {
+
+constexpr int kCus = 256;   // compute units: each holds one 8-wave block or two 4-wave blocks
+
+// Kernel form for NB batch tiles.  One round of blocks, one per compute unit,
+// streams best, so a block takes the fewest row groups (1, 2, 4 or 8) with
+// which the launch still is one.  With fewer it runs in more rounds (1128
+// groups x 8192 columns: 208 us at 8 groups per block, 239 us at 4), with more
+// it leaves units idle (752 groups x 8192: 200 us at 8, 124 us at 4; 500 groups
+// x 8192: 182, 106 and 82 us at 8, 4 and 2).  Past one round 8-wave blocks
+// (each fills its unit) stay ahead while the last round is nearly full (8020
+// groups x 4096, 120 states: 895 against 973 us), else 4-wave blocks, two to a
+// unit, leave the shorter tail (2500 groups x 4096: 208 against 243 us).  With
+// one batch tile the waves share nothing, and a nearly full round is 1 to 3%
+// faster in 4-wave blocks (1940 groups x 7800: 295 against 297 us; 2000 x 4096:
+// 153 against 161 us), a full one with the weights in bursts (2000 x 8192: 307
+// against 317 us; 1940 groups: 299 against 295 us).
+template <int EPI, int NB>
+void launch_packed_nb(const void *h, int64_t h_head_stride, const void *w, const void *bias, float *z, void *hout,
+                      int B, int hidden, int rows, int n_heads, float *gmax, hipStream_t st) {
+  const int nG = packed_row_groups(rows), nS = packed_k_steps(hidden);
+  auto go = [&](auto kern, int waves, int groups) {
+    dim3 grid((nG + groups - 1) / groups, n_heads, (B + 16 * NB - 1) / (16 * NB));
+    hipLaunchKernelGGL(kern, grid, dim3(64 * waves), 0, st, static_cast<const uint16_t *>(h), h_head_stride,
+                       static_cast<const uint4 *>(w), static_cast<const uint16_t *>(bias), z,
+                       static_cast<uint16_t *>(hout), B, hidden, rows, n_heads, nG, nS, gmax);
+  };
+  auto blocks = [&](int groups) { return (int64_t)((nG + groups - 1) / groups) * n_heads; };
+  const int64_t rounds = (blocks(8) + kCus - 1) / kCus;
+  if (blocks(1) <= kCus) {
+    go(packed_gemm<4, NB, 4, (NB <= 4 ? 2 : 1), EPI>, 4, 1);
+  } else if (blocks(2) <= kCus) {
+    if constexpr (NB >= 6) go(packed_gemm<8, NB, 4, (NB == 6 ? 2 : 1), EPI>, 8, 2);
+    else go(packed_gemm<4, NB, 2, 4, EPI>, 4, 2);
+  } else if (blocks(4) <= kCus) {
+    go(packed_gemm<8, NB, 2, (NB >= 6 ? 2 : 4), EPI>, 8, 4);
+  } else if (NB == 1 ? blocks(8) * 8 <= kCus * 7 : rounds == 1 || blocks(8) * 10 >= rounds * kCus * 9) {
+    go(packed_gemm<8, NB, 1, 4, EPI>, 8, 8);
+  } else if (NB == 1 && blocks(8) * 100 >= rounds * kCus * 97) {
+    if constexpr (NB == 1) go(packed_gemm<4, 1, 1, 4, EPI, true>, 4, 4);
+  } else {
+    go(packed_gemm<4, NB, 1, 4, EPI>, 4, 4);
+  }
+}
+
+template <int EPI>
+hipError_t launch_packed(const void *h, int64_t h_head_stride, const void *w, const void *bias, float *z, void *hout,
+                         int B, int hidden, int rows, int n_heads, float *gmax, hipStream_t st) {
+  // batch tiles of a block: the fewest of 1, 2, 4, 6, 8 that hold the batch (past 128 states, groups of 128);
+  // the shared states are addressed with 32 bits from a group's first row, which 2^24 columns could exceed
+  auto kern = B <= 16 || hidden >= 1 << 24 ? launch_packed_nb<EPI, 1>
+              : B <= 32                          ? launch_packed_nb<EPI, 2>
+              : B <= 64                          ? launch_packed_nb<EPI, 4>
+              : B <= 96                          ? launch_packed_nb<EPI, 6>
+                                                 : launch_packed_nb<EPI, 8>;
+  kern(h, h_head_stride, w, bias, z, hout, B, hidden, rows, n_heads, gmax, st);
+  return hipGetLastError();
+}
+
+}  // namespace
+
 hipError_t launch_head_logits(int dt, const void *h, int64_t h_head_stride, const void *w, bool packed, float *z,
                               int B, int hidden, int vocab, int n_heads, hipStream_t st, float *gmax) {
-  if (dt == 1 && packed) {
-    const int nb = B <= 16 ? 1 : 2;
-    const int nG = packed_row_groups(vocab), nS = packed_k_steps(hidden);
-    dim3 grid((nG + kWaves - 1) / kWaves, n_heads, (B + 16 * nb - 1) / (16 * nb));
-    auto kern = nb == 1 ? head_logits_packed<1> : head_logits_packed<2>;
-    hipLaunchKernelGGL(kern, grid, dim3(kWaves * 64), 0, st, static_cast<const uint16_t *>(h), h_head_stride,
-                       static_cast<const uint4 *>(w), z, B, hidden, vocab, n_heads, nG, nS, gmax);
-  } else if (dt == 1) {
+  if (dt == 1 && packed)
+    return launch_packed<0>(h, h_head_stride, w, nullptr, z, nullptr, B, hidden, vocab, n_heads, gmax, st);
+  if (dt == 1) {
     const int nb = B <= 16 ? 1 : 2;
     dim3 grid((vocab + kWaves * kRowsPerWave - 1) / (kWaves * kRowsPerWave), n_heads,
               (B + 16 * nb - 1) / (16 * nb));
@@ -702,20 +735,11 @@ hipError_t launch_head_logits(int dt, const void *h, int64_t h_head_stride, cons
 
 hipError_t launch_resblock(int dt, const void *h, const void *w1, const void *b1, void *out, int B, int hidden,
                            int n_heads, hipStream_t st) {
-  if (dt == 1) {
-    const int nb = B <= 16 ? 1 : 2;
-    const int nG = packed_row_groups(hidden), nS = packed_k_steps(hidden);
-    dim3 grid(nG, n_heads, (B + 16 * nb - 1) / (16 * nb));
-    auto kern = nb == 1 ? resblock_packed<1> : resblock_packed<2>;
-    hipLaunchKernelGGL(kern, grid, dim3(kResSplit * 64), 0, st, static_cast<const uint16_t *>(h),
-                       static_cast<const uint4 *>(w1), static_cast<const uint16_t *>(b1),
-                       static_cast<uint16_t *>(out), B, hidden, nG, nS);
-  } else {
-    dim3 grid((hidden + 3) / 4, n_heads);
-    hipLaunchKernelGGL(head_logits_f32<1>, grid, dim3(256), 0, st, static_cast<const float *>(h), (int64_t)0,
-                       static_cast<const float *>(w1), nullptr, static_cast<const float *>(b1),
-                       static_cast<float *>(out), B, hidden, hidden, n_heads);
-  }
+  if (dt == 1) return launch_packed<1>(h, 0, w1, b1, nullptr, out, B, hidden, hidden, n_heads, nullptr, st);
+  dim3 grid((hidden + 3) / 4, n_heads);
+  hipLaunchKernelGGL(head_logits_f32<1>, grid, dim3(256), 0, st, static_cast<const float *>(h), (int64_t)0,
+                     static_cast<const float *>(w1), nullptr, static_cast<const float *>(b1),
+                     static_cast<float *>(out), B, hidden, hidden, n_heads);
   return hipGetLastError();
 }
 

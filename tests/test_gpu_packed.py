@@ -1,0 +1,92 @@
+"""GPU: the packed-weight kernel at the edges of its forms.
+
+The launch picks the batch tiles of a block (1, 2, 4, 6 or 8 of 16 states) from
+the batch, and the row groups and k ranges of a block from the number of row
+groups; the k steps divide into pipelined groups, the ranges' rests and a last
+partial step.  Sizes sit on both sides of every such line.  References are fp64;
+|error| <= (hidden + 8) 2^-24 sum |w h| (fp32 summation in any order), and for
+the residual blocks half a bf16 step more (of eight significant bits: 2^-8 of
+the value).
+"""
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_2506_01986_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+# heads, batch, vocabulary, hidden: 64-row groups x heads against 256 blocks of 1, 2, 4 and 8 groups
+HEADS = [
+    (3, 1, 64, 40), (4, 16, 4096, 136), (4, 33, 4090, 264), (2, 129, 700, 1000), (4, 97, 4096, 520),    # one group
+    (4, 5, 4160, 1000), (4, 17, 8192, 264), (4, 64, 5001, 136), (4, 96, 8190, 72), (2, 128, 10000, 392),  # two
+    (4, 16, 8256, 264), (4, 32, 16384, 40), (4, 65, 9001, 328), (4, 113, 16380, 136),                    # four
+    (4, 10, 16448, 136), (4, 40, 28000, 72), (4, 96, 20001, 40), (4, 128, 32760, 264),                   # eight
+    (4, 3, 32760, 520), (4, 16, 31000, 264), (4, 12, 37000, 136), (4, 18, 37003, 72), (4, 200, 36992, 40),
+]
+
+
+def bits(rng, shape, std):
+    return synth.to_bf16_bits((std * rng.standard_normal(shape)).astype(np.float32)).reshape(shape)
+
+
+@pytest.fixture(scope="module")
+def gpu():
+    import torch
+    from paper_2506_01986_amd import runner, specmemo as sm
+    assert torch.cuda.is_available(), "GPU tests need a visible GPU"
+    sm.load()
+    return torch, sm, lambda x: runner.to_device(x, "bf16", "cuda")
+
+
+def pack(torch, sm, w):
+    n, rows, hidden = w.shape
+    out = torch.empty(sm.packed_heads_bytes(sm.BF16, n, rows, hidden), dtype=torch.uint8, device="cuda")
+    sm.pack_heads(sm.BF16, n, rows, hidden, w, out)
+    return out
+
+
+@pytest.mark.parametrize("n_heads,B,vocab,hidden", HEADS)
+def test_heads_forms(gpu, n_heads, B, vocab, hidden):
+    torch, sm, dev = gpu
+    rng = np.random.default_rng(B + vocab + hidden)
+    h, w = bits(rng, (B, hidden), 1.0), bits(rng, (n_heads, vocab, hidden), 0.05)
+    hd, wd = dev(h), dev(w)
+    wp = pack(torch, sm, wd)
+    z = torch.full((B, n_heads, vocab), float("nan"), device="cuda")
+    k = 10
+    ids = torch.empty((B, n_heads, k), dtype=torch.int32, device="cuda")
+    zero = np.zeros(B, np.int32)
+    tr = sm.Trees(np.arange(B + 1), np.full(B, -1), zero, zero, device="cuda")       # single-node trees
+    tok, root = (torch.zeros(B, dtype=torch.int32, device="cuda") for _ in range(2))
+    nb = sm.workspace_bytes(sm.WS_TOPK, sm.BF16, tr, None, n_heads, vocab)
+    ws = torch.empty(nb, dtype=torch.uint8, device="cuda")
+    sm.medusa_topk(sm.BF16, tr, hidden, vocab, n_heads, [k] * n_heads, hd, wp, root, ids, tok, logits_out=z, ws=ws,
+                   ws_bytes=nb, head_layout=sm.HEADS_PACKED)
+    for i in range(n_heads):
+        w64 = wd[i].double().t()
+        ref, size = hd.double() @ w64, hd.double().abs() @ w64.abs()
+        err = (z[:, i].double() - ref).abs() - (hidden + 8) * 2.0 ** -24 * size
+        assert float(err.max()) <= 0 and bool(torch.isfinite(z[:, i]).all())
+    if B * vocab <= 400_000:      # the group maxima lead to the same ids as the logits themselves
+        want, _ = oracle.topk(z.cpu().numpy().astype(np.float64).reshape(B * n_heads, vocab), k)
+        assert np.array_equal(ids.cpu().numpy().reshape(B * n_heads, k), want)
+
+
+@pytest.mark.parametrize("n_heads,B,hidden", [(2, 1, 8), (4, 16, 520), (3, 34, 1000), (5, 70, 392), (2, 120, 4104),
+                                              (4, 33, 4160), (4, 130, 136)])
+def test_resblock_forms(gpu, n_heads, B, hidden):
+    torch, sm, dev = gpu
+    rng = np.random.default_rng(B + hidden)
+    h, w, b = bits(rng, (B, hidden), 1.0), bits(rng, (n_heads, hidden, hidden), 0.05), bits(rng, (n_heads, hidden), 0.5)
+    hd, wd, bd = dev(h), dev(w), dev(b)
+    out = torch.full((n_heads, B, hidden), float("nan"), dtype=torch.bfloat16, device="cuda")
+    sm.medusa_resblock(sm.BF16, B, hidden, n_heads, hd, pack(torch, sm, wd), bd, out)
+    for i in range(n_heads):
+        y = hd.double() @ wd[i].double().t() + bd[i].double()
+        ref = hd.double() + y * torch.sigmoid(y)
+        size = hd.double().abs() @ wd[i].double().abs().t() + bd[i].double().abs()
+        # |SiLU'| <= 1.1; the activation itself adds a few ulp of y
+        bound = 1.1 * (hidden + 8) * 2.0 ** -24 * size + 2.0 ** -20 * (1 + y.abs()) + 2.0 ** -8 * ref.abs()
+        assert float(((out[i].double() - ref).abs() - bound).max()) <= 0
