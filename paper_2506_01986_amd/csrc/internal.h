@@ -69,6 +69,18 @@ struct AttnItem {
   uint16_t s, kvh, ch, rb;
 };
 
+// The same for a launch of up to kMaxSeqPacked sequences whose KV heads are a
+// multiple of eight: every XCD then runs the same number of blocks of each
+// sequence, so one prefix count serves all eight, and a pool of under 2^32 rows
+// has 32-bit bases.
+struct AttnSeqPacked {
+  uint32_t base;
+  int32_t L, node0, ch_len, part0;   // as in AttnSeq
+  int32_t cum, ccum;                 // blocks and combine blocks of an XCD before this sequence
+  uint16_t N, nch;
+};
+constexpr int kMaxSeqPacked = 120;
+
 struct AttnArgs {
   const void *q;
   void *out;
@@ -84,13 +96,20 @@ struct AttnArgs {
   const AttnItem *cmap;    // combine blocks: sequence, KV head, row block
   int64_t cap_total;
   int32_t n_q, n_kv, group, head_dim;
+  int32_t rb;              // query rows per work item (bf16 path)
   float scale_log2;        // scale * log2(e)
   float scale;
   int32_t nseq, items, citems;   // items: blocks of the launch (XCD order: padded)
   int32_t xcd_order;        // nonzero: consecutive work items share an XCD
-  int32_t xcd_cum[8][kMaxSeqPerLaunch + 1];   // XCD order: blocks of XCD x before sequence s
-  int32_t xcd_ccum[8][kMaxSeqPerLaunch + 1];  // XCD order: combine blocks of XCD x before sequence s
-  AttnSeq seq[kMaxSeqPerLaunch];
+  int32_t packed;           // nonzero: the descriptors are pseq (XCD order, no padding blocks)
+  union {
+    struct {
+      int32_t xcd_cum[8][kMaxSeqPerLaunch + 1];   // XCD order: blocks of XCD x before sequence s
+      int32_t xcd_ccum[8][kMaxSeqPerLaunch + 1];  // XCD order: combine blocks of XCD x before sequence s
+      AttnSeq seq[kMaxSeqPerLaunch];
+    };
+    AttnSeqPacked pseq[kMaxSeqPacked];
+  };
 };
 
 static_assert(sizeof(AttnArgs) <= 4096, "kernel arguments are limited to 4 KB");
@@ -103,7 +122,7 @@ constexpr int kAttnHeadDim = 128;
 __host__ __device__ constexpr int64_t attn_partial_floats(int rows_per_block) {
   return (int64_t)rows_per_block * (kAttnHeadDim / 2 + 2);
 }
-hipError_t launch_tree_attn_bf16(const AttnArgs &a, int rows_per_block, hipStream_t st);
+hipError_t launch_tree_attn_bf16(const AttnArgs &a, hipStream_t st);
 // Static scratch of the allocation-free attention entry point: its size, and
 // this device's address of it (looked up once per device, on first use).
 constexpr size_t kAttnStaticScratchBytes = size_t(32) << 20;

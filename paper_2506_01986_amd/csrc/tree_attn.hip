@@ -70,6 +70,35 @@ __device__ __forceinline__ AttnSeq pick_seq(const AttnSeq &d, int s) {
   return r;
 }
 
+// Packed descriptors (kMaxSeqPacked sequences, two per lane): the sequence that
+// holds block k of an XCD (COMBINE: combine block k), by two ballots over the
+// prefix counts.  Fills S; S.item0 is the prefix count of what was searched.
+// Every load is issued at once, one memory latency.
+template <bool COMBINE>
+__device__ __forceinline__ int find_packed(const AttnArgs &a, int k, AttnSeq &S) {
+  const int lane = threadIdx.x & 63;
+  static_assert(kMaxSeqPacked > 64 && kMaxSeqPacked <= 128, "two per lane");
+  const AttnSeqPacked lo = a.pseq[lane], hi = a.pseq[min(lane + 64, kMaxSeqPacked - 1)];
+  // a sequence of one chunk has no combine block: its prefix count equals its successor's, which the search passes on to
+  const uint64_t le0 = __builtin_amdgcn_ballot_w64(lane < a.nseq && (COMBINE ? lo.ccum : lo.cum) <= k);
+  const uint64_t le1 = __builtin_amdgcn_ballot_w64(lane + 64 < a.nseq && (COMBINE ? hi.ccum : hi.cum) <= k);
+  const int s = __builtin_popcountll(le0) + __builtin_popcountll(le1) - 1;
+  const bool up = s >= 64;
+  const int l = s & 63;
+  auto get = [&](int v0, int v1) { return up ? rl(v1, l) : rl(v0, l); };
+  const int nn = get(lo.N | lo.nch << 16, hi.N | hi.nch << 16);
+  S.base = (uint32_t)get((int)lo.base, (int)hi.base);
+  S.L = get(lo.L, hi.L);
+  S.node0 = get(lo.node0, hi.node0);
+  S.ch_len = get(lo.ch_len, hi.ch_len);
+  S.part0 = get(lo.part0, hi.part0);
+  S.item0 = COMBINE ? get(lo.ccum, hi.ccum) : get(lo.cum, hi.cum);
+  S.N = nn & 0xFFFF;
+  S.nch = (uint32_t)nn >> 16;
+  S.nrb = (S.N * a.group + a.rb - 1) / a.rb;
+  return s;
+}
+
 // Work item and sequence descriptor of block `bid`; false for a padding block.
 // Every load is issued up front (one memory latency): the per-lane copies of
 // the sequence descriptors and, for the XCD order, of XCD x's block counts.
@@ -85,6 +114,7 @@ __device__ __forceinline__ AttnSeq pick_seq(const AttnSeq &d, int s) {
 // multiple) every XCD gets one KV head of every sequence.  xcd_cum[x][s] is
 // the number of XCD x's blocks before sequence s; blocks past the busiest
 // XCD's work are padding.
+template <bool PACKED>
 __device__ __forceinline__ bool decode_item(const AttnArgs &a, int bid, Item &it, AttnSeq &S) {
   if (a.map) {   // table mode: the host decoded every block's item (same order as below)
     const AttnItem m = a.map[bid];
@@ -94,6 +124,15 @@ __device__ __forceinline__ bool decode_item(const AttnArgs &a, int bid, Item &it
     it.ch = m.ch;
     it.rb = m.rb;
     S = a.tab[m.s];
+    return true;
+  }
+  if constexpr (PACKED) {   // no padding blocks: every XCD runs the same number of blocks
+    const int x = bid & 7, k = bid >> 3;
+    it.s = find_packed<false>(a, k, S);
+    const int kk = k - S.item0, per_unit = S.nch * S.nrb;
+    it.kvh = x + 8 * (kk / per_unit);
+    it.ch = kk % per_unit / S.nrb;
+    it.rb = kk % S.nrb;
     return true;
   }
   const int lane = threadIdx.x & 63;
@@ -192,7 +231,8 @@ __device__ __forceinline__ int vswz(int r, int c) { return c ^ ((r & 3) << 2); }
 // waves on every SIMD.
 // MINB: blocks that must fit on one compute unit (bounds the registers).
 // PAD: the cache holds pad tokens (padded batching), flagged in a.key_valid.
-template <int WAVES, int SLOTS, int MINB, bool PAD, int KSPLIT>
+// PACKED: the descriptors are a.pseq.
+template <int WAVES, int SLOTS, int MINB, bool PAD, int KSPLIT, bool PACKED>
 __global__ __launch_bounds__(WAVES * 64, MINB) void tree_attn_bf16(AttnArgs a) {
   static_assert(SLOTS == 2 || SLOTS == 3, "ring depth");
   static_assert(KSPLIT == 1 || KSPLIT == 2, "key split");
@@ -211,7 +251,7 @@ __global__ __launch_bounds__(WAVES * 64, MINB) void tree_attn_bf16(AttnArgs a) {
 
   Item it;
   AttnSeq S;
-  if (!decode_item(a, blockIdx.x, it, S)) return;   // padding block: no work, no barrier reached
+  if (!decode_item<PACKED>(a, blockIdx.x, it, S)) return;   // padding block: no work, no barrier reached
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int rwave = wave % RW, ksb = wave / RW;     // row group and key group of this wave
   const int h = lane >> 5;              // which half of the wave
@@ -495,6 +535,22 @@ __global__ __launch_bounds__(WAVES * 64, MINB) void tree_attn_bf16(AttnArgs a) {
     softmax_tail(Sc, pk);
     pv(vring[slot], pk);
   };
+
+  // A wave whose rows all lie past the last one (16 nodes of a multi-head batch
+  // leave half of a 64-row item empty) only loads and waits, in step with the
+  // others: the matrix cores are theirs (96 sequences of 16 nodes, 32 heads, 64
+  // to 512 keys: 103 us before, with the packed descriptors).
+  const bool wave_rows = it.rb * RB + __builtin_amdgcn_readfirstlane(rwave) * 32 < rows;
+  if (KSPLIT == 2 && !wave_rows)
+    for (int j = 0; j < ntiles; ++j) {
+      wait_loads(SLOTS == 3 && j + 1 < ntiles ? 2 : 0);
+      ring_barrier();
+      if (j + SLOTS - 1 < ntiles) {
+        issue_k(j + SLOTS - 1);
+        issue_v(j + SLOTS - 1);
+      }
+    }
+  else
   for (int j = 0; j < ntiles; j += SLOTS) {
     tile(j, std::integral_constant<int, 0>{});
     if (j + 1 < ntiles) tile(j + 1, std::integral_constant<int, 1>{});
@@ -569,7 +625,7 @@ __global__ __launch_bounds__(WAVES * 64, MINB) void tree_attn_bf16(AttnArgs a) {
 // query row, each with 32 head-dim columns, and one pass over the chunks with
 // a running max (the partials hold unnormalised O in bf16, the chunk's max m
 // and sum l in fp32), the loads of four chunks in flight at once.
-template <int RB>
+template <int RB, bool PACKED>
 __global__ __launch_bounds__(4 * RB) void tree_attn_combine(AttnArgs a) {
   constexpr int CPT = D / 4;   // columns per thread
   const int idx = blockIdx.x, lane = threadIdx.x & 63;
@@ -577,9 +633,15 @@ __global__ __launch_bounds__(4 * RB) void tree_attn_combine(AttnArgs a) {
   int kvh, rb;
   AttnSeq S;
   AttnSeq mine{};
-  if (!a.cmap && lane < kMaxSeqPerLaunch) mine = a.seq[lane];
-  const int ccum = !a.cmap && lane <= kMaxSeqPerLaunch ? a.xcd_ccum[x][lane] : 0;
-  if (a.cmap) {   // table mode: the host decoded every block's row block
+  const bool in_args = !a.cmap && !PACKED;
+  if (in_args && lane < kMaxSeqPerLaunch) mine = a.seq[lane];
+  const int ccum = in_args && lane <= kMaxSeqPerLaunch ? a.xcd_ccum[x][lane] : 0;
+  if constexpr (PACKED) {
+    find_packed<true>(a, k, S);
+    const int kk = k - S.item0;
+    kvh = x + 8 * (kk / S.nrb);
+    rb = kk % S.nrb;
+  } else if (a.cmap) {   // table mode: the host decoded every block's row block
     const AttnItem m = a.cmap[idx];
     if (m.s == 0xFFFF) return;
     S = a.tab[m.s];
@@ -742,26 +804,26 @@ __global__ __launch_bounds__(256) void tree_attn_f32(AttnArgs a, int node_begin,
 }  // namespace
 
 namespace {
-template <bool PAD>
-void launch_bf16(const AttnArgs &a, int rows_per_block, hipStream_t st) {
-  if (rows_per_block == 64) {
-    hipLaunchKernelGGL((tree_attn_bf16<4, 2, 2, PAD, 2>), dim3(a.items), dim3(256), 0, st, a);
-    if (a.citems) hipLaunchKernelGGL(tree_attn_combine<64>, dim3(a.citems), dim3(256), 0, st, a);
-  } else if (rows_per_block == 128) {
-    hipLaunchKernelGGL((tree_attn_bf16<4, 2, 2, PAD, 1>), dim3(a.items), dim3(256), 0, st, a);
-    if (a.citems) hipLaunchKernelGGL(tree_attn_combine<128>, dim3(a.citems), dim3(512), 0, st, a);
+template <bool PAD, bool PACKED>
+void launch_bf16(const AttnArgs &a, hipStream_t st) {
+  if (a.rb == 64) {
+    hipLaunchKernelGGL((tree_attn_bf16<4, 2, 2, PAD, 2, PACKED>), dim3(a.items), dim3(256), 0, st, a);
+    if (a.citems) hipLaunchKernelGGL((tree_attn_combine<64, PACKED>), dim3(a.citems), dim3(256), 0, st, a);
+  } else if (a.rb == 128) {
+    hipLaunchKernelGGL((tree_attn_bf16<4, 2, 2, PAD, 1, PACKED>), dim3(a.items), dim3(256), 0, st, a);
+    if (a.citems) hipLaunchKernelGGL((tree_attn_combine<128, PACKED>), dim3(a.citems), dim3(512), 0, st, a);
   } else {
-    hipLaunchKernelGGL((tree_attn_bf16<8, 3, 1, PAD, 1>), dim3(a.items), dim3(512), 0, st, a);
-    if (a.citems) hipLaunchKernelGGL(tree_attn_combine<256>, dim3(a.citems), dim3(1024), 0, st, a);
+    hipLaunchKernelGGL((tree_attn_bf16<8, 3, 1, PAD, 1, PACKED>), dim3(a.items), dim3(512), 0, st, a);
+    if (a.citems) hipLaunchKernelGGL((tree_attn_combine<256, PACKED>), dim3(a.citems), dim3(1024), 0, st, a);
   }
 }
 }  // namespace
 
-hipError_t launch_tree_attn_bf16(const AttnArgs &a, int rows_per_block, hipStream_t st) {
+hipError_t launch_tree_attn_bf16(const AttnArgs &a, hipStream_t st) {
   if (a.key_valid)
-    launch_bf16<true>(a, rows_per_block, st);
+    a.packed ? launch_bf16<true, true>(a, st) : launch_bf16<true, false>(a, st);
   else
-    launch_bf16<false>(a, rows_per_block, st);
+    a.packed ? launch_bf16<false, true>(a, st) : launch_bf16<false, false>(a, st);
   return hipGetLastError();
 }
 

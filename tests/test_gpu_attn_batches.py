@@ -1,0 +1,37 @@
+"""GPU: attention of batches whose descriptors travel packed in the kernel
+arguments (33 to 120 sequences, KV heads a multiple of eight), and items with
+waves that hold no query row.  Both sides of the limits, against the oracle.
+"""
+
+import numpy as np
+import pytest
+
+from paper_2506_01986_amd import synth
+
+from tests.test_gpu_parity import edge_cfg, run_parity, torch_cuda  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+def lens(n, hi, *first):
+    return [*first, *(int(x) for x in np.random.default_rng(n).integers(0, hi, n - len(first)))]
+
+
+# sequences, query heads, KV heads, most tree nodes, committed lengths
+BATCHES = {
+    "b33_mha_few_rows": (33, 8, 8, 20, lens(33, 200)),           # 64-row items, second wave group often empty
+    "b64_split": (64, 8, 8, 64, lens(64, 300, 6000, 2500, 0)),   # some sequences in several chunks, one empty
+    "b65_gqa": (65, 32, 8, 40, lens(65, 150, 3000)),             # 128-row items, row blocks with one to four waves
+    "b120_kv16": (120, 16, 16, 6, lens(120, 90, 700)),           # the most sequences in the arguments
+    "b121": (121, 8, 8, 6, lens(121, 90, 700)),                  # one more: the workspace table
+    "b40_kv12": (40, 12, 12, 10, lens(40, 200, 900)),            # KV heads not a multiple of eight: the table
+}
+
+
+@pytest.mark.parametrize("name", list(BATCHES))
+def test_batches(torch_cuda, name):  # noqa: F811
+    B, n_q, n_kv, nodes, L = BATCHES[name]
+    rng = np.random.default_rng(B)
+    trees = [synth.random_tree(rng, int(rng.integers(1, nodes + 1))) for _ in range(B)]
+    cfg = edge_cfg(B=B, n_q=n_q, n_kv=n_kv, hidden=32, vocab=256)
+    run_parity(torch_cuda, synth.make(cfg, trees=trees, lens=L), label=name)
