@@ -490,7 +490,7 @@ int specmemo_plan_tree_sizes(int32_t B, const int32_t *seq_len_h, const int32_t 
  *   SPECMEMO_WS_TOPK:   kv ignored; n_q_or_heads = n_heads; vocab used (the
  *                       fp32 logits, none when logits_out is given; bf16 also
  *                       the maxima of 64-row groups, which let the top-k pass
- *                       with packed heads read only the groups that can hold a
+ *                       read only the groups that can hold a
  *                       top-k value; without room for them it scans every
  *                       logit, with the same result).
  *   SPECMEMO_WS_ATTN:   kv required; n_q_or_heads = n_q; vocab ignored.

@@ -444,7 +444,7 @@ int accept_args(specmemo_dtype dt, const specmemo_trees *t, int32_t vocab, specm
 }
 
 // Top-k workspace: the fp32 logits (unless the caller keeps them), then, for
-// packed bf16 heads, the maxima of the 64-row groups (the top-k pass reads
+// bf16 heads, the maxima of the 64-row groups (the top-k pass reads
 // only the groups that can hold a top-k value).
 size_t topk_logit_bytes(int B, int n_heads, int vocab) { return align256((size_t)B * n_heads * vocab * sizeof(float)); }
 size_t topk_gmax_bytes(int B, int n_heads, int vocab) {
@@ -550,7 +550,7 @@ int specmemo_medusa_topk(specmemo_dtype dt, const specmemo_trees *t, int32_t hid
   float *z = logits_out ? logits_out : static_cast<float *>(ws);
   // the group maxima, where the workspace holds them (else every logit is scanned)
   float *gmax = nullptr;
-  if (head_layout == SPECMEMO_HEADS_PACKED && ws && al(ws, 16) && ws_bytes >= need + topk_gmax_bytes(ti.B, n_heads, vocab))
+  if (dt == SPECMEMO_BF16 && ws && al(ws, 16) && ws_bytes >= need + topk_gmax_bytes(ti.B, n_heads, vocab))
     gmax = reinterpret_cast<float *>(static_cast<uint8_t *>(ws) + need);
   hipStream_t st = static_cast<hipStream_t>(stream);
   const int64_t h_head_stride = per_head_input ? (int64_t)ti.B * hidden : 0;

@@ -38,7 +38,7 @@ struct TopkArgs {
 };
 
 // h_head_stride: elements between the heads' inputs (0: every head reads the same h).
-// gmax non-null (packed bf16 only): also the maxima of 64-row groups, [B][n_heads][nG].
+// gmax non-null (bf16 only): also the maxima of 64-row groups, [B][n_heads][nG].
 hipError_t launch_head_logits(int dt, const void *h, int64_t h_head_stride, const void *w, bool packed, float *z,
                               int B, int hidden, int vocab, int n_heads, hipStream_t st, float *gmax = nullptr);
 // Medusa residual blocks: out[i][b] = h[b] + SiLU(W1_i h[b] + b1_i); bf16 W1 packed like the heads.

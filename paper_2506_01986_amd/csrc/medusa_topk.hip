@@ -9,7 +9,7 @@
 // HBM-bound for any batch of a verify step, so waves stream 64 vocabulary rows
 // each with 16-byte loads and contract them on the 16x16x32 bf16 matrix cores
 // (batch padded to 16s: the padding costs matrix-core time that is far below
-// the load time).  Packed heads: packed_gemm; row-major ones: head_logits_bf16.
+// the load time).  Packed heads: head_gemm; row-major ones: head_logits_bf16.
 #include <type_traits>
 
 #include "device.h"
@@ -18,101 +18,6 @@
 namespace specmemo {
 
 namespace {
-
-constexpr int kRowsPerWave = 64;   // four 16-row A tiles
-constexpr int kWaves = 4;
-constexpr int kUnroll = 2;         // k-steps of 32 issued before their MFMAs
-
-template <int NB>   // 16-wide batch tiles contracted per weight load
-__global__ __launch_bounds__(kWaves * 64) void head_logits_bf16(
-    const uint16_t *__restrict__ h, int64_t h_head_stride, const uint16_t *__restrict__ W, float *__restrict__ z,
-    int B, int hidden, int vocab, int n_heads) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int head = blockIdx.y, b0 = blockIdx.z * 16 * NB;
-  const int gwave = blockIdx.x * kWaves + wave;
-  const int row0 = gwave * kRowsPerWave;
-  if (row0 >= vocab) return;
-  const int r16 = lane & 15, kq = lane >> 4;
-
-  const uint16_t *wp[4];
-#pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    int row = min(row0 + t * 16 + r16, vocab - 1);
-    wp[t] = W + ((int64_t)head * vocab + row) * hidden + kq * 8;
-  }
-  bool bvalid[NB];
-  const uint16_t *hp[NB];
-#pragma unroll
-  for (int n = 0; n < NB; ++n) {
-    int b = b0 + 16 * n + r16;
-    bvalid[n] = b < B;
-    hp[n] = h + head * h_head_stride + (int64_t)(bvalid[n] ? b : 0) * hidden + kq * 8;
-  }
-
-  f32x4 acc[NB][4];
-#pragma unroll
-  for (int n = 0; n < NB; ++n)
-#pragma unroll
-    for (int t = 0; t < 4; ++t) acc[n][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  // Every wave starts its k sweep at a different step: all waves reading their
-  // rows (16 KB apart) at the same offset would load the same HBM channels.
-  const int steps = hidden / (32 * kUnroll);
-  const int rot = steps ? (gwave + head * 977) % steps : 0;
-  for (int s0 = 0; s0 < steps; ++s0) {
-    const int k = (s0 + rot < steps ? s0 + rot : s0 + rot - steps) * 32 * kUnroll;
-    uint4 a[kUnroll][4], bq[kUnroll][NB];
-#pragma unroll
-    for (int u = 0; u < kUnroll; ++u) {
-#pragma unroll
-      for (int t = 0; t < 4; ++t) a[u][t] = *reinterpret_cast<const uint4 *>(wp[t] + k + 32 * u);
-#pragma unroll
-      for (int n = 0; n < NB; ++n)
-        bq[u][n] = ld16_or_zero(bvalid[n], hp[n] + k + 32 * u);
-    }
-#pragma unroll
-    for (int u = 0; u < kUnroll; ++u)
-#pragma unroll
-      for (int n = 0; n < NB; ++n) {
-        bf16x8 bv = __builtin_bit_cast(bf16x8, bq[u][n]);
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-          acc[n][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[u][t]),
-                                                              bv, acc[n][t], 0, 0, 0);
-      }
-  }
-  int k = steps * 32 * kUnroll;
-  for (; k < hidden; k += 32) {   // tail: hidden % 8 == 0, so a lane's 8 elements are all in or all out
-    const bool in = k + kq * 8 < hidden;
-    uint4 a[4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t) a[t] = ld16_or_zero(in, wp[t] + k);
-#pragma unroll
-    for (int n = 0; n < NB; ++n) {
-      uint4 bq = ld16_or_zero(in && bvalid[n], hp[n] + k);
-      bf16x8 bv = __builtin_bit_cast(bf16x8, bq);
-#pragma unroll
-      for (int t = 0; t < 4; ++t)
-        acc[n][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[t]), bv,
-                                                            acc[n][t], 0, 0, 0);
-    }
-  }
-
-  // C layout: lane holds column (batch) lane&15, rows 4*(lane>>4) + 0..3 of each tile.
-#pragma unroll
-  for (int n = 0; n < NB; ++n) {
-    const int b = b0 + 16 * n + (lane & 15);
-    if (b >= B) continue;
-    float *zr = z + ((int64_t)b * n_heads + head) * vocab;
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      int row = row0 + t * 16 + 4 * kq;
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        if (row + j < vocab) zr[row + j] = acc[n][t][j];
-    }
-  }
-}
 
 // Weights are read once per step: nontemporal loads keep them from displacing
 // the hidden states and logits in the caches.
@@ -131,7 +36,7 @@ __device__ __forceinline__ uint4 ld16_stream(const uint4 *p) {
 // when 32 states were the most that shared a stream).
 //
 // KS waves share a row group and split its k steps in contiguous ranges, whose
-// partial sums meet in LDS: see launch_packed_nb for when.
+// partial sums meet in LDS: see launch_gemm_nb for when.
 //
 // Weights: PRE k steps (4 KB each) in flight per wave, a step's registers
 // refilled right after its products; BURST (one batch tile): eight steps at a
@@ -151,7 +56,7 @@ __device__ __forceinline__ uint4 ld16_stream(const uint4 *p) {
 __device__ __forceinline__ int state_slot_swz(int r) { return ((r >> 1) ^ (r >> 2)) & 3; }
 
 template <int NW, int NB, int KS, int KC, int EPI, bool BURST = false>
-__global__ __launch_bounds__(64 * NW, 8 / NW) void packed_gemm(
+__global__ __launch_bounds__(64 * NW, 8 / NW) void head_gemm(
     const uint16_t *__restrict__ h, int64_t h_head_stride, const uint4 *__restrict__ Wp,
     const uint16_t *__restrict__ bias, float *__restrict__ z, uint16_t *__restrict__ hout, int B, int hidden, int rows,
     int n_heads, int nG, int nS, float *__restrict__ gmax) {
@@ -348,6 +253,142 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void packed_gemm(
             o[row + j] = f32_to_bf16(bf16_to_f32(hin[row + j]) + y / (1.f + expf(-y)));
           }
       }
+    }
+  }
+}
+
+// Row-major heads (nn.Linear layout), up to 16 NB states.  A matrix operand
+// loaded to registers takes 64 bytes of each of 16 rows per instruction, which
+// the memory system serves at 4.7 TB/s; so the weights go to LDS directly, 256
+// bytes of each of 4 rows per instruction, and are read there in operand order.
+// Eight waves of 16 rows share the states of a chunk of 128 columns; a ring of
+// SLOTS chunks is filled by direct loads and ordered by vmcnt waits and one
+// bare barrier per chunk.  A row's 16-byte part c sits at c ^ (row % 16): 16
+// rows read at one part lie in distinct banks.  hidden % 128 columns follow
+// from registers.  Blocks start their sweeps at different chunks: rows a power
+// of two apart, read at one offset by all blocks, keep to a few memory channels
+// (rows of 8192: 498 us without, 355 us with; of 5120: 215 and 217 us).
+// 4 heads, 4 states, 32003 x 5120: 268 -> 217 us; 10 states, 32000 x 8192: 402 ->
+// 355 us (5.9 TB/s); 16 states, 18001 x 5120: 283 -> 149 us; 40 states, 32000 x
+// 4096, one weight stream instead of two: 453 -> 196 us.  gmax: as in head_gemm.
+template <int NB, int SLOTS>
+__global__ __launch_bounds__(512, 2) void head_rows(const uint16_t *__restrict__ h, int64_t h_head_stride,
+                                                    const uint8_t *__restrict__ W, float *__restrict__ z, int B,
+                                                    int hidden, int rows, int n_heads, int nG,
+                                                    float *__restrict__ gmax) {
+  constexpr int kRow = 256;                                   // bytes of a row per chunk
+  constexpr int kW = 128 * kRow, kSlot = kW + 16 * NB * kRow;
+  constexpr int kLoads = 4 + NB;                              // direct loads per wave and chunk
+  __shared__ __attribute__((aligned(1024))) uint8_t ring[SLOTS * kSlot];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int head = blockIdx.y, b0 = blockIdx.z * 16 * NB;
+  const int r16 = lane & 15, kq = lane >> 4;
+  const int row0 = blockIdx.x * 128 + wave * 16, last = rows - 1;
+  const int nc = hidden < 1 << 27 ? hidden >> 7 : 0;          // whole chunks (rows past 2^27 columns: all from registers)
+  const int rot = nc ? (int)((blockIdx.x + 7u * head) % (unsigned)nc) : 0;
+  // Load i of a wave: LDS rows 4 i + lane / 16 of its tile, part lane % 16 of
+  // the slot's row, which holds the row's part (lane % 16) ^ (row % 16).
+  const uint8_t *wb = uniform_ptr(W + ((int64_t)head * rows + min(row0, last)) * hidden * 2);
+  const uint16_t *hb = h + head * h_head_stride;
+  const uint8_t *hb8 = uniform_ptr(reinterpret_cast<const uint8_t *>(hb + (int64_t)b0 * hidden));
+  uint32_t woff[4], hoff[NB];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int r = 4 * i + kq;
+    woff[i] = (uint32_t)min(r, max(last - row0, 0)) * (uint32_t)(2 * hidden) + 16u * (r16 ^ r);   // rows past the last repeat it
+  }
+  // states: 4 NB loads per chunk, spread over the waves (waves 4 to 7 repeat those of 0 to 3)
+#pragma unroll
+  for (int n = 0; n < NB; ++n) {
+    const int r = 4 * (wave & 3) + kq;
+    hoff[n] = (uint32_t)min(16 * n + r, B - 1 - b0) * (uint32_t)(2 * hidden) + 16u * (r16 ^ r);
+  }
+  const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_void_t *)ring);
+  auto issue = [&](int c, int slot) {
+    const int cc = c + rot < nc ? c + rot : c + rot - nc;
+    const uint32_t base = lds0 + slot * kSlot;
+#pragma unroll
+    for (int n = 0; n < NB; ++n) lds_load16(hb8 + (int64_t)kRow * cc, hoff[n], base + kW + (16 * n + 4 * (wave & 3)) * kRow);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) lds_load16(wb + (int64_t)kRow * cc, woff[i], base + (16 * wave + 4 * i) * kRow);
+  };
+  f32x4 acc[NB][2];
+#pragma unroll
+  for (int n = 0; n < NB; ++n) acc[n][0] = acc[n][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int c = 0; c < SLOTS - 1; ++c)
+    if (c < nc) issue(c, c);
+  auto chunk = [&](int c, auto slot_c) {
+    constexpr int slot = decltype(slot_c)::value;
+    // chunks issued after this one: up to SLOTS - 2
+    const int later = min(nc - 1 - c, SLOTS - 2);
+    if (later >= 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * kLoads) : "memory");
+    else if (later == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kLoads) : "memory");
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    ring_barrier();      // every wave's loads of this chunk are in, and its reads of the slot refilled next are done
+    if (c + SLOTS - 1 < nc) issue(c + SLOTS - 1, (slot + SLOTS - 1) % SLOTS);
+    const uint8_t *s = ring + slot * kSlot;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int part = 16 * ((4 * u + kq) ^ r16);
+      const bf16x8 a = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4_t *>(s + (16 * wave + r16) * kRow + part));
+#pragma unroll
+      for (int n = 0; n < NB; ++n) {
+        const bf16x8 b = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4_t *>(s + kW + (16 * n + r16) * kRow + part));
+        acc[n][u & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc[n][u & 1], 0, 0, 0);
+      }
+    }
+  };
+  for (int c = 0; c < nc; c += SLOTS) {
+    chunk(c, std::integral_constant<int, 0>{});
+    if (c + 1 < nc) chunk(c + 1, std::integral_constant<int, 1>{});
+    if constexpr (SLOTS >= 3)
+      if (c + 2 < nc) chunk(c + 2, std::integral_constant<int, 2>{});
+    if constexpr (SLOTS == 4)
+      if (c + 3 < nc) chunk(c + 3, std::integral_constant<int, 3>{});
+  }
+  const uint8_t *wr = wb + (int64_t)min(r16, max(last - row0, 0)) * hidden * 2;
+  for (int k = (nc << 7) + 8 * kq; k - 8 * kq < hidden; k += 32) {   // the last hidden % 128 columns
+    const bf16x8 a = __builtin_bit_cast(bf16x8, ld16_or_zero(k < hidden, wr + 2 * (int64_t)k));
+#pragma unroll
+    for (int n = 0; n < NB; ++n) {
+      const int b = b0 + 16 * n + r16;
+      const bool in = b < B && k < hidden;
+      const bf16x8 hv = __builtin_bit_cast(bf16x8, ld16_or_zero(in, hb + (int64_t)(in ? b : 0) * hidden + (in ? k : 0)));
+      acc[n][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, hv, acc[n][0], 0, 0, 0);
+    }
+  }
+  float (*tops)[16 * NB] = reinterpret_cast<float (*)[16 * NB]>(ring);   // [wave][state]: maximum of the wave's 16 rows
+  if (gmax) ring_barrier();                                   // every wave is past its reads of the ring
+#pragma unroll
+  for (int n = 0; n < NB; ++n) {
+    const int b = b0 + 16 * n + r16, row = row0 + 4 * kq;
+    const f32x4 v = acc[n][0] + acc[n][1];
+    if (gmax) {
+      float m = -INFINITY;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) m = row + j < rows ? fmaxf(m, v[j]) : m;
+      m = fmaxf(m, __shfl_xor(m, 16));
+      m = fmaxf(m, __shfl_xor(m, 32));
+      if (kq == 0) tops[wave][16 * n + r16] = m;
+    }
+    if (b >= B) continue;
+    float *zr = z + ((int64_t)b * n_heads + head) * rows + row;
+    if ((rows & 3) == 0) {
+      if (row < rows) *reinterpret_cast<f32x4 *>(zr) = v;
+    } else {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (row + j < rows) zr[j] = v[j];
+    }
+  }
+  if (gmax) {
+    __syncthreads();
+    for (int i = threadIdx.x; i < 32 * NB; i += 512) {        // the block's two 64-row groups
+      const int g = i / (16 * NB), c = i % (16 * NB), G = 2 * blockIdx.x + g, b = b0 + c;
+      if (G < nG && b < B)
+        gmax[((int64_t)b * n_heads + head) * nG + G] =
+            fmaxf(fmaxf(tops[4 * g][c], tops[4 * g + 1][c]), fmaxf(tops[4 * g + 2][c], tops[4 * g + 3][c]));
     }
   }
 }
@@ -671,7 +712,7 @@ constexpr int kCus = 256;   // compute units: each holds one 8-wave block or two
 // 153 against 161 us), a full one with the weights in bursts (2000 x 8192: 307
 // against 317 us; 1940 groups: 299 against 295 us).
 template <int EPI, int NB>
-void launch_packed_nb(const void *h, int64_t h_head_stride, const void *w, const void *bias, float *z, void *hout,
+void launch_gemm_nb(const void *h, int64_t h_head_stride, const void *w, const void *bias, float *z, void *hout,
                       int B, int hidden, int rows, int n_heads, float *gmax, hipStream_t st) {
   const int nG = packed_row_groups(rows), nS = packed_k_steps(hidden);
   auto go = [&](auto kern, int waves, int groups) {
@@ -683,31 +724,31 @@ void launch_packed_nb(const void *h, int64_t h_head_stride, const void *w, const
   auto blocks = [&](int groups) { return (int64_t)((nG + groups - 1) / groups) * n_heads; };
   const int64_t rounds = (blocks(8) + kCus - 1) / kCus;
   if (blocks(1) <= kCus) {
-    go(packed_gemm<4, NB, 4, (NB <= 4 ? 2 : 1), EPI>, 4, 1);
+    go(head_gemm<4, NB, 4, (NB <= 4 ? 2 : 1), EPI>, 4, 1);
   } else if (blocks(2) <= kCus) {
-    if constexpr (NB >= 6) go(packed_gemm<8, NB, 4, (NB == 6 ? 2 : 1), EPI>, 8, 2);
-    else go(packed_gemm<4, NB, 2, 4, EPI>, 4, 2);
+    if constexpr (NB >= 6) go(head_gemm<8, NB, 4, (NB == 6 ? 2 : 1), EPI>, 8, 2);
+    else go(head_gemm<4, NB, 2, 4, EPI>, 4, 2);
   } else if (blocks(4) <= kCus) {
-    go(packed_gemm<8, NB, 2, (NB >= 6 ? 2 : 4), EPI>, 8, 4);
+    go(head_gemm<8, NB, 2, (NB >= 6 ? 2 : 4), EPI>, 8, 4);
   } else if (NB == 1 ? blocks(8) * 8 <= kCus * 7 : rounds == 1 || blocks(8) * 10 >= rounds * kCus * 9) {
-    go(packed_gemm<8, NB, 1, 4, EPI>, 8, 8);
+    go(head_gemm<8, NB, 1, 4, EPI>, 8, 8);
   } else if (NB == 1 && blocks(8) * 100 >= rounds * kCus * 97) {
-    if constexpr (NB == 1) go(packed_gemm<4, 1, 1, 4, EPI, true>, 4, 4);
+    if constexpr (NB == 1) go(head_gemm<4, 1, 1, 4, EPI, true>, 4, 4);
   } else {
-    go(packed_gemm<4, NB, 1, 4, EPI>, 4, 4);
+    go(head_gemm<4, NB, 1, 4, EPI>, 4, 4);
   }
 }
 
 template <int EPI>
-hipError_t launch_packed(const void *h, int64_t h_head_stride, const void *w, const void *bias, float *z, void *hout,
+hipError_t launch_gemm(const void *h, int64_t h_head_stride, const void *w, const void *bias, float *z, void *hout,
                          int B, int hidden, int rows, int n_heads, float *gmax, hipStream_t st) {
   // batch tiles of a block: the fewest of 1, 2, 4, 6, 8 that hold the batch (past 128 states, groups of 128);
   // the shared states are addressed with 32 bits from a group's first row, which 2^24 columns could exceed
-  auto kern = B <= 16 || hidden >= 1 << 24 ? launch_packed_nb<EPI, 1>
-              : B <= 32                          ? launch_packed_nb<EPI, 2>
-              : B <= 64                          ? launch_packed_nb<EPI, 4>
-              : B <= 96                          ? launch_packed_nb<EPI, 6>
-                                                 : launch_packed_nb<EPI, 8>;
+  auto kern = B <= 16 || hidden >= 1 << 24 ? launch_gemm_nb<EPI, 1>
+              : B <= 32                          ? launch_gemm_nb<EPI, 2>
+              : B <= 64                          ? launch_gemm_nb<EPI, 4>
+              : B <= 96                          ? launch_gemm_nb<EPI, 6>
+                                                 : launch_gemm_nb<EPI, 8>;
   kern(h, h_head_stride, w, bias, z, hout, B, hidden, rows, n_heads, gmax, st);
   return hipGetLastError();
 }
@@ -717,14 +758,15 @@ hipError_t launch_packed(const void *h, int64_t h_head_stride, const void *w, co
 hipError_t launch_head_logits(int dt, const void *h, int64_t h_head_stride, const void *w, bool packed, float *z,
                               int B, int hidden, int vocab, int n_heads, hipStream_t st, float *gmax) {
   if (dt == 1 && packed)
-    return launch_packed<0>(h, h_head_stride, w, nullptr, z, nullptr, B, hidden, vocab, n_heads, gmax, st);
+    return launch_gemm<0>(h, h_head_stride, w, nullptr, z, nullptr, B, hidden, vocab, n_heads, gmax, st);
   if (dt == 1) {
-    const int nb = B <= 16 ? 1 : 2;
-    dim3 grid((vocab + kWaves * kRowsPerWave - 1) / (kWaves * kRowsPerWave), n_heads,
-              (B + 16 * nb - 1) / (16 * nb));
-    auto kern = nb == 1 ? head_logits_bf16<1> : head_logits_bf16<2>;
-    hipLaunchKernelGGL(kern, grid, dim3(kWaves * 64), 0, st, static_cast<const uint16_t *>(h), h_head_stride,
-                       static_cast<const uint16_t *>(w), z, B, hidden, vocab, n_heads);
+    // batch tiles of a block: the fewest of 1, 2, 4, 8 that hold the batch; a ring as deep as LDS allows.  The
+    // states are addressed with 32 bits from a block's first row, which 2^24 columns could exceed.
+    const int nb = B <= 16 || hidden >= 1 << 24 ? 1 : B <= 32 ? 2 : B <= 64 ? 4 : 8;
+    const dim3 grid((vocab + 127) / 128, n_heads, (B + 16 * nb - 1) / (16 * nb));
+    auto kern = nb == 1 ? head_rows<1, 4> : nb == 2 ? head_rows<2, 3> : nb == 4 ? head_rows<4, 3> : head_rows<8, 2>;
+    hipLaunchKernelGGL(kern, grid, dim3(512), 0, st, static_cast<const uint16_t *>(h), h_head_stride,
+                       static_cast<const uint8_t *>(w), z, B, hidden, vocab, n_heads, packed_row_groups(vocab), gmax);
   } else {
     dim3 grid((vocab + 3) / 4, n_heads);
     hipLaunchKernelGGL(head_logits_f32<0>, grid, dim3(256), 0, st, static_cast<const float *>(h), h_head_stride,
@@ -735,7 +777,7 @@ hipError_t launch_head_logits(int dt, const void *h, int64_t h_head_stride, cons
 
 hipError_t launch_resblock(int dt, const void *h, const void *w1, const void *b1, void *out, int B, int hidden,
                            int n_heads, hipStream_t st) {
-  if (dt == 1) return launch_packed<1>(h, 0, w1, b1, nullptr, out, B, hidden, hidden, n_heads, nullptr, st);
+  if (dt == 1) return launch_gemm<1>(h, 0, w1, b1, nullptr, out, B, hidden, hidden, n_heads, nullptr, st);
   dim3 grid((hidden + 3) / 4, n_heads);
   hipLaunchKernelGGL(head_logits_f32<1>, grid, dim3(256), 0, st, static_cast<const float *>(h), (int64_t)0,
                      static_cast<const float *>(w1), nullptr, static_cast<const float *>(b1),

@@ -180,36 +180,9 @@ __device__ __forceinline__ float tile_max32(const f32x16 (&x)[2]) {
   return fmaxf(fmaxf(u0, u1), fmaxf(u2, u3));
 }
 
-typedef __attribute__((address_space(3))) void lds_void_t;
 typedef short s16x4_t __attribute__((__vector_size__(8)));
 typedef __attribute__((address_space(3))) s16x4_t lds_s16x4_t;
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
-
-// 16-byte direct load of every lane into LDS at lds_base + 16 * lane (one
-// global_load_lds_dwordx4 with M0 = lds_base, which must be wave-uniform),
-// from the wave-uniform base `src` (SGPRs) plus this lane's 32-bit byte
-// offset.  It is issued from inline assembly so that the compiler does not
-// guard later LDS reads with waits for it: the tile ring orders these loads
-// with explicit vmcnt waits.  M0 must be written one wait state before the load.
-// A wave-uniform pointer, made explicit for the compiler (so that it stays in
-// SGPRs, as the base operand of the direct loads requires).
-template <typename T>
-__device__ __forceinline__ T *uniform_ptr(T *p) {
-  const uint64_t b = reinterpret_cast<uintptr_t>(p);
-  return reinterpret_cast<T *>((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(b >> 32)) << 32 |
-                               (uint32_t)__builtin_amdgcn_readfirstlane((int)b));
-}
-
-__device__ __forceinline__ void lds_load16(const void *src, uint32_t off, uint32_t lds_base) {
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(src), "s"(lds_base)
-               : "memory", "m0");
-}
-
-// Workgroup barrier for the LDS tile ring.  The tile loads into LDS are
-// ordered by explicit vmcnt waits; a __syncthreads() would also wait for the
-// loads still in flight for later tiles (its release fence waits for every
-// outstanding vector memory operation) and so shorten the prefetch distance.
-__device__ __forceinline__ void ring_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 // LDS swizzles (16-byte chunk index c of tile row r).  K rows are read 16 rows
 // at a time at one chunk (MFMA A operand): chunk c of row r sits at c ^ (r % 16).

@@ -1,6 +1,6 @@
-"""GPU: the packed-weight kernel at the edges of its forms.
+"""GPU: the projection kernels at the edges of their forms.
 
-The launch picks the batch tiles of a block (1, 2, 4, 6 or 8 of 16 states) from
+Packed weights: the launch picks the batch tiles of a block (1, 2, 4, 6 or 8 of 16 states) from
 the batch, and the row groups and k ranges of a block from the number of row
 groups; the k steps divide into pipelined groups, the ranges' rests and a last
 partial step.  Sizes sit on both sides of every such line.  References are fp64;
@@ -47,15 +47,20 @@ def pack(torch, sm, w):
     return out
 
 
-@pytest.mark.parametrize("n_heads,B,vocab,hidden", HEADS)
-def test_heads_forms(gpu, n_heads, B, vocab, hidden):
+# row-major: 128-row blocks, 128-column chunks (rings of 2, 3 and 4), 1 to 8 batch tiles
+ROWS = [(3, 1, 1, 8), (2, 16, 128, 128), (4, 5, 129, 392), (4, 16, 4003, 1000), (4, 17, 1000, 256), (3, 32, 255, 520),
+        (4, 33, 2001, 640), (2, 64, 130, 1160), (2, 65, 700, 136), (4, 120, 1001, 384), (1, 200, 300, 904)]
+
+
+@pytest.mark.parametrize("packed,n_heads,B,vocab,hidden", [(True, *c) for c in HEADS] + [(False, *c) for c in ROWS])
+def test_heads_forms(gpu, packed, n_heads, B, vocab, hidden):
     torch, sm, dev = gpu
     rng = np.random.default_rng(B + vocab + hidden)
     h, w = bits(rng, (B, hidden), 1.0), bits(rng, (n_heads, vocab, hidden), 0.05)
     hd, wd = dev(h), dev(w)
-    wp = pack(torch, sm, wd)
+    wp = pack(torch, sm, wd) if packed else wd
     z = torch.full((B, n_heads, vocab), float("nan"), device="cuda")
-    k = 10
+    k = min(10, vocab)
     ids = torch.empty((B, n_heads, k), dtype=torch.int32, device="cuda")
     zero = np.zeros(B, np.int32)
     tr = sm.Trees(np.arange(B + 1), np.full(B, -1), zero, zero, device="cuda")       # single-node trees
@@ -63,7 +68,7 @@ def test_heads_forms(gpu, n_heads, B, vocab, hidden):
     nb = sm.workspace_bytes(sm.WS_TOPK, sm.BF16, tr, None, n_heads, vocab)
     ws = torch.empty(nb, dtype=torch.uint8, device="cuda")
     sm.medusa_topk(sm.BF16, tr, hidden, vocab, n_heads, [k] * n_heads, hd, wp, root, ids, tok, logits_out=z, ws=ws,
-                   ws_bytes=nb, head_layout=sm.HEADS_PACKED)
+                   ws_bytes=nb, head_layout=sm.HEADS_PACKED if packed else sm.HEADS_ROWMAJOR)
     for i in range(n_heads):
         w64 = wd[i].double().t()
         ref, size = hd.double() @ w64, hd.double().abs() @ w64.abs()
