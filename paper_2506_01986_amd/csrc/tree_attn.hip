@@ -692,86 +692,123 @@ __global__ __launch_bounds__(4 * RB) void tree_attn_combine(AttnArgs a) {
                   pack_bf16x2(o[8 * q + 4] * inv, o[8 * q + 5] * inv), pack_bf16x2(o[8 * q + 6] * inv, o[8 * q + 7] * inv)};
 }
 
-// fp32 path: one wave per (node, query head); lanes own head-dimension elements
-// and walk the key set in order (the committed keys in batches of sixteen).
-__global__ __launch_bounds__(256) void tree_attn_f32(AttnArgs a, int node_begin, int node_count) {
-  const int lane = threadIdx.x & 63;
-  const int w = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (w >= node_count * a.n_q) return;
-  const int gnode = node_begin + w / a.n_q, hq = w % a.n_q;
-  int s = 0;
-  while (s + 1 < a.nseq && a.seq[s + 1].node0 <= gnode) ++s;
+// fp32 path: one block per (node, query head).  Bound by latency (the whole
+// cache of the fp32 workload is 128 KB), so the key range is spread as far as
+// it goes: LPK lanes hold a key's row (4 columns each), a wave takes 64 / LPK
+// keys per load and kF32Batch loads at once, the block's four waves take
+// batches in turn, and each key slot runs its own online softmax; the slots'
+// (m, l, o) meet in LDS at the end.  16 nodes, 4 heads, 128 keys: 35 us with
+// one wave per (node, head), one key per load and a six-step reduction each.
+constexpr int kF32Batch = 4;
+
+template <int LPK>
+__global__ __launch_bounds__(256) void tree_attn_f32(AttnArgs a, int node_begin) {
+  constexpr int KPW = 64 / LPK, P = 4 * KPW;       // keys per load and wave, key slots of the block
+  __shared__ int par[kMaxNodes], path[kMaxPath];
+  __shared__ int path_len;
+  __shared__ float pm[P], pl[P];
+  __shared__ float po[P][4 * LPK];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int gnode = node_begin + blockIdx.x, hq = blockIdx.y;
+  const int s = find_seq(a.nseq, lane < kMaxSeqPerLaunch ? a.seq[lane].node0 : 0, gnode);
   const AttnSeq &S = a.seq[s];
-  const int n = gnode - S.node0, kvh = hq / a.group, d = a.head_dim;
-  const float *q = static_cast<const float *>(a.q) + ((int64_t)gnode * a.n_q + hq) * d;
-  const float *K = static_cast<const float *>(a.k) + ((int64_t)kvh * a.cap_total + S.base) * d;
-  const float *V = static_cast<const float *>(a.v) + ((int64_t)kvh * a.cap_total + S.base) * d;
-  const bool e0 = lane < d, e1 = lane + 64 < d;
-  const float q0 = e0 ? q[lane] : 0.f, q1 = e1 ? q[lane + 64] : 0.f;
-  float m = -INFINITY, l = 0.f, o0 = 0.f, o1 = 0.f;
-  auto dot = [&](float k0, float k1) {
-    float p = q0 * k0 + q1 * k1;
+  const int n = gnode - S.node0, kvh = hq / a.group, d = a.head_dim, N = S.N, L = S.L;
+  if (tid < N) par[tid] = a.parent[S.node0 + tid];
+  const int sl = lane / LPK, c = 4 * (lane % LPK), slot = wave * KPW + sl;
+  const bool in = c < d;                           // head_dim % 4 == 0
+  const int cc = in ? c : 0;
+  const float *K = static_cast<const float *>(a.k) + ((int64_t)kvh * a.cap_total + S.base) * d + cc;
+  const float *V = static_cast<const float *>(a.v) + ((int64_t)kvh * a.cap_total + S.base) * d + cc;
+  f32x4 q = *reinterpret_cast<const f32x4 *>(static_cast<const float *>(a.q) + ((int64_t)gnode * a.n_q + hq) * d + cc);
+  if (!in) q = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  float m = -INFINITY, l = 0.f;
+  f32x4 o = {0.f, 0.f, 0.f, 0.f};
+  // kF32Batch keys of this slot: rows row[u], taken where use[u]
+  auto batch = [&](const int (&row)[kF32Batch], const bool (&use)[kF32Batch]) {
+    f32x4 k[kF32Batch], v[kF32Batch];
+    float sc[kF32Batch];
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) p += __shfl_xor(p, off);
-    return p;
-  };
-  auto update = [&](float p, float v0, float v1) {   // online softmax, one key
-    const float s = p * a.scale;
-    const float mn = fmaxf(m, s);
-    const float alpha = expf(m - mn), pe = expf(s - mn);
-    l = l * alpha + pe;
-    o0 = o0 * alpha + pe * v0;
-    o1 = o1 * alpha + pe * v1;
-    m = mn;
-  };
-  // Committed keys sixteen at a time: the batch's row loads are issued
-  // together and its reductions are independent; the batch then moves the
-  // running max once and adds its weights.  Pad tokens (padded batching) are
-  // skipped: weight 0.
-  constexpr int KB = 16;
-  for (int t0 = 0; t0 < S.L; t0 += KB) {
-    float k0[KB], k1[KB], v0[KB], v1[KB], pp[KB];
-    bool use[KB];
-#pragma unroll
-    for (int u = 0; u < KB; ++u) {
-      const int t = min(t0 + u, S.L - 1);
-      const int64_t r = S.base + t;
-      use[u] = t0 + u < S.L && (!a.key_valid || ((a.key_valid[r >> 5] >> (r & 31)) & 1u));
-      k0[u] = e0 ? K[(int64_t)t * d + lane] : 0.f;
-      k1[u] = e1 ? K[(int64_t)t * d + lane + 64] : 0.f;
-      v0[u] = e0 ? V[(int64_t)t * d + lane] : 0.f;
-      v1[u] = e1 ? V[(int64_t)t * d + lane + 64] : 0.f;
+    for (int u = 0; u < kF32Batch; ++u) {
+      k[u] = *reinterpret_cast<const f32x4 *>(K + (int64_t)row[u] * d);
+      v[u] = *reinterpret_cast<const f32x4 *>(V + (int64_t)row[u] * d);
+      if (!in) k[u] = f32x4{0.f, 0.f, 0.f, 0.f};   // columns past head_dim add nothing to a score
     }
-#pragma unroll
-    for (int u = 0; u < KB; ++u) pp[u] = dot(k0[u], k1[u]);
     float mb = m;
 #pragma unroll
-    for (int u = 0; u < KB; ++u)
-      if (use[u]) mb = fmaxf(mb, pp[u] * a.scale);
-    if (mb > m) {   // m = -inf on the first visible key: alpha = 0
+    for (int u = 0; u < kF32Batch; ++u) {
+      float p = q[0] * k[u][0] + q[1] * k[u][1] + (q[2] * k[u][2] + q[3] * k[u][3]);
+#pragma unroll
+      for (int off = 1; off < LPK; off <<= 1) p += __shfl_xor(p, off);
+      sc[u] = p * a.scale;
+      if (use[u]) mb = fmaxf(mb, sc[u]);
+    }
+    if (mb > m) {                                  // m = -inf before the slot's first visible key: alpha = 0
       const float alpha = expf(m - mb);
       l *= alpha;
-      o0 *= alpha;
-      o1 *= alpha;
+      o *= alpha;
       m = mb;
     }
 #pragma unroll
-    for (int u = 0; u < KB; ++u)
+    for (int u = 0; u < kF32Batch; ++u)
       if (use[u]) {
-        const float pe = expf(pp[u] * a.scale - m);
+        const float pe = expf(sc[u] - m);
         l += pe;
-        o0 = fmaf(pe, v0[u], o0);
-        o1 = fmaf(pe, v1[u], o1);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = fmaf(pe, v[u][e], o[e]);
       }
+  };
+  // Committed keys; pad tokens (padded batching) are skipped: weight 0.
+  for (int t0 = wave * KPW * kF32Batch; t0 < L; t0 += P * kF32Batch) {
+    int row[kF32Batch];
+    bool use[kF32Batch];
+#pragma unroll
+    for (int u = 0; u < kF32Batch; ++u) {
+      const int t = t0 + u * KPW + sl;
+      row[u] = min(t, L - 1);
+      const int64_t r = S.base + row[u];
+      use[u] = t < L && (!a.key_valid || ((a.key_valid[r >> 5] >> (r & 31)) & 1u));
+    }
+    batch(row, use);
   }
-  for (int u = n; u >= 0; u = a.parent[S.node0 + u]) {   // the node's tree rows: its root path
-    const int64_t row = S.L + u;
-    const float p = dot(e0 ? K[row * d + lane] : 0.f, e1 ? K[row * d + lane + 64] : 0.f);
-    update(p, e0 ? V[row * d + lane] : 0.f, e1 ? V[row * d + lane + 64] : 0.f);
+  // The node's tree rows, its root path: at most kMaxPath keys, dealt to the slots.
+  __syncthreads();
+  if (tid == 0) {
+    int len = 0;
+    for (int u = n; u >= 0 && len < kMaxPath; u = par[u]) path[len++] = u;
+    path_len = len;
   }
-  float *out = static_cast<float *>(a.out) + ((int64_t)gnode * a.n_q + hq) * d;
-  if (e0) out[lane] = o0 / l;
-  if (e1) out[lane + 64] = o1 / l;
+  __syncthreads();
+  {
+    const int len = path_len;
+    int row[kF32Batch];
+    bool use[kF32Batch];
+#pragma unroll
+    for (int u = 0; u < kF32Batch; ++u) {
+      const int i = u * P + slot;
+      use[u] = i < len;
+      row[u] = L + path[i < len ? i : 0];
+    }
+    static_assert(kF32Batch * P >= kMaxPath, "one batch takes the longest path");
+    batch(row, use);
+  }
+  if (lane % LPK == 0) {
+    pm[slot] = m;
+    pl[slot] = l;
+  }
+  *reinterpret_cast<f32x4 *>(&po[slot][c]) = o;
+  __syncthreads();
+  if (tid >= d) return;
+  float M = -INFINITY, lsum = 0.f, acc = 0.f;
+#pragma unroll
+  for (int i = 0; i < P; ++i) M = fmaxf(M, pm[i]); // finite: the node's own row is visible
+#pragma unroll
+  for (int i = 0; i < P; ++i) {
+    const float w = expf(pm[i] - M);               // a slot without a visible key: 0
+    lsum = fmaf(pl[i], w, lsum);
+    acc = fmaf(po[i][tid], w, acc);
+  }
+  static_cast<float *>(a.out)[((int64_t)gnode * a.n_q + hq) * d + tid] = acc / lsum;
 }
 
 }  // namespace
@@ -828,8 +865,8 @@ hipError_t attn_static_scratch(void **ptr) {
 }
 
 hipError_t launch_tree_attn_f32(const AttnArgs &a, int node_begin, int node_count, hipStream_t st) {
-  const int waves = node_count * a.n_q;
-  hipLaunchKernelGGL(tree_attn_f32, dim3((waves + 3) / 4), dim3(256), 0, st, a, node_begin, node_count);
+  auto kern = a.head_dim <= 32 ? tree_attn_f32<8> : a.head_dim <= 64 ? tree_attn_f32<16> : tree_attn_f32<32>;
+  hipLaunchKernelGGL(kern, dim3(node_count, a.n_q), dim3(256), 0, st, a, node_begin);
   return hipGetLastError();
 }
 
