@@ -161,8 +161,29 @@ def _i32(x) -> np.ndarray:
     return np.ascontiguousarray(np.asarray(x, dtype=np.int32))
 
 
-class Trees:
+class _HostMirrors:
+    """Addresses of the numpy arrays named in ``_MIRRORS``, kept from their
+    assignment on: asking numpy costs about 1.2 us an array, 20 us of a small
+    step's calls.  Assigning a mirror drops them; device pointers are asked for
+    on every call."""
+
+    _MIRRORS = ()
+
+    def __setattr__(self, name, value):
+        object.__setattr__(self, name, value)
+        if name in self._MIRRORS:
+            object.__setattr__(self, "_addr", None)
+
+    def _addresses(self):
+        if self._addr is None:
+            object.__setattr__(self, "_addr", tuple(getattr(self, n).ctypes.data for n in self._MIRRORS))
+        return self._addr
+
+
+class Trees(_HostMirrors):
     """Ragged batch of candidate trees: device arrays plus host mirrors."""
+
+    _MIRRORS = ("node_off_h", "parent_h", "depth_h", "rank_h")
 
     def __init__(self, node_off, parent, depth, rank, device=None, dev_arrays=None):
         self.node_off_h, self.parent_h = _i32(node_off), _i32(parent)
@@ -184,12 +205,13 @@ class Trees:
         return int(self.depth_h.max())
 
     def struct(self) -> _Trees:
-        return _Trees(self.B, *[_ptr(t) for t in self.dev],
-                      *[a.ctypes.data for a in (self.node_off_h, self.parent_h, self.depth_h, self.rank_h)])
+        return _Trees(self.B, *[_ptr(t) for t in self.dev], *self._addresses())
 
 
-class KVPool:
+class KVPool(_HostMirrors):
     """One layer's budget-capped KV pool: device K, V and seq_len, host mirrors."""
+
+    _MIRRORS = ("seq_base_h", "seq_cap_h", "seq_len_h")
 
     def __init__(self, k, v, seq_len_dev, seq_base, seq_cap, seq_len):
         self.k, self.v, self.seq_len = k, v, seq_len_dev
@@ -200,8 +222,7 @@ class KVPool:
 
     def struct(self) -> _KV:
         return _KV(_ptr(self.k), _ptr(self.v), self.cap_total, self.n_kv, self.head_dim,
-                   _ptr(self.seq_len), self.seq_base_h.ctypes.data, self.seq_cap_h.ctypes.data,
-                   self.seq_len_h.ctypes.data)
+                   _ptr(self.seq_len), *self._addresses())
 
 
 def abi_version() -> int:

@@ -319,3 +319,19 @@ def test_noalloc_attention_checks_and_scratch_limit():
     r = subprocess.run([sys.executable, "-c", child], cwd=root, capture_output=True, text=True, timeout=120,
                        env={**os.environ, "SPECMEMO_ATTN_CHUNK": "64", "HIP_VISIBLE_DEVICES": ""})
     assert r.returncode == 0 and r.stdout.startswith("ok"), r.stdout + r.stderr
+
+
+def test_reassigned_mirrors_are_followed():
+    """Host addresses kept by the binding follow every assignment of a mirror."""
+    import copy
+    trees = sm.Trees([0, 2], [-1, 0], [0, 1], [0, 0], dev_arrays=[FAKE] * 4)
+    pool = sm.KVPool(np.zeros((1, 8, 128), np.float32), FAKE, FAKE, [0], [8], [3])
+    for obj, names in ((trees, ("node_off", "parent", "depth", "rank")), (pool, ("seq_base", "seq_cap", "seq_len"))):
+        first = obj.struct()
+        other = copy.copy(obj)
+        for n in names:
+            host = getattr(obj, n + "_h")
+            assert getattr(first, n + "_h") == host.ctypes.data
+            setattr(other, n + "_h", host.copy())
+            assert getattr(other.struct(), n + "_h") == getattr(other, n + "_h").ctypes.data != host.ctypes.data
+            assert getattr(obj.struct(), n + "_h") == host.ctypes.data
