@@ -164,15 +164,19 @@ def _i32(x) -> np.ndarray:
 class _HostMirrors:
     """Addresses of the numpy arrays named in ``_MIRRORS``, kept from their
     assignment on: asking numpy costs about 1.2 us an array, 20 us of a small
-    step's calls.  Assigning a mirror drops them; device pointers are asked for
-    on every call."""
+    step's calls.  Assigning a mirror drops them, and a copied or unpickled
+    object asks anew; device pointers are asked for on every call."""
 
     _MIRRORS = ()
+    _addr = None
 
     def __setattr__(self, name, value):
         object.__setattr__(self, name, value)
         if name in self._MIRRORS:
             object.__setattr__(self, "_addr", None)
+
+    def __getstate__(self):
+        return {**self.__dict__, "_addr": None}
 
     def _addresses(self):
         if self._addr is None:

@@ -335,3 +335,16 @@ def test_reassigned_mirrors_are_followed():
             setattr(other, n + "_h", host.copy())
             assert getattr(other.struct(), n + "_h") == getattr(other, n + "_h").ctypes.data != host.ctypes.data
             assert getattr(obj.struct(), n + "_h") == host.ctypes.data
+
+
+def test_copied_mirrors_have_their_own_addresses():
+    """Copies and unpickled objects hold other arrays than their original."""
+    import copy
+    import pickle
+    trees = sm.Trees([0, 2], [-1, 0], [0, 1], [0, 0], dev_arrays=[None] * 4)
+    pool = sm.KVPool(np.zeros((1, 8, 128), np.float32), None, None, [0], [8], [3])
+    for obj in (trees, pool):
+        obj._addresses()
+        for other in (copy.copy(obj), copy.deepcopy(obj), pickle.loads(pickle.dumps(obj))):
+            assert other._addresses() == tuple(getattr(other, n).ctypes.data for n in obj._MIRRORS)
+        assert copy.deepcopy(obj)._addresses() != obj._addresses()
