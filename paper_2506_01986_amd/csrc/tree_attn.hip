@@ -709,7 +709,7 @@ __global__ __launch_bounds__(256) void tree_attn_f32(AttnArgs a, int node_begin)
   __shared__ float pm[P], pl[P];
   __shared__ float po[P][4 * LPK];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int gnode = node_begin + blockIdx.x, hq = blockIdx.y;
+  const int gnode = node_begin + blockIdx.y, hq = blockIdx.x;   // up to 32 x 128 nodes; heads have no such limit
   const int s = find_seq(a.nseq, lane < kMaxSeqPerLaunch ? a.seq[lane].node0 : 0, gnode);
   const AttnSeq &S = a.seq[s];
   const int n = gnode - S.node0, kvh = hq / a.group, d = a.head_dim, N = S.N, L = S.L;
@@ -752,7 +752,8 @@ __global__ __launch_bounds__(256) void tree_attn_f32(AttnArgs a, int node_begin)
 #pragma unroll
     for (int u = 0; u < kF32Batch; ++u)
       if (use[u]) {
-        const float pe = expf(sc[u] - m);
+        // a slot that has met only scores of -inf (overflowed products) gives them weight 0, as its neighbours do
+        const float pe = sc[u] == -INFINITY ? 0.f : expf(sc[u] - m);
         l += pe;
 #pragma unroll
         for (int e = 0; e < 4; ++e) o[e] = fmaf(pe, v[u][e], o[e]);
@@ -866,7 +867,7 @@ hipError_t attn_static_scratch(void **ptr) {
 
 hipError_t launch_tree_attn_f32(const AttnArgs &a, int node_begin, int node_count, hipStream_t st) {
   auto kern = a.head_dim <= 32 ? tree_attn_f32<8> : a.head_dim <= 64 ? tree_attn_f32<16> : tree_attn_f32<32>;
-  hipLaunchKernelGGL(kern, dim3(node_count, a.n_q), dim3(256), 0, st, a, node_begin);
+  hipLaunchKernelGGL(kern, dim3(a.n_q, node_count), dim3(256), 0, st, a, node_begin);
   return hipGetLastError();
 }
 

@@ -6,9 +6,10 @@ waves that hold no query row.  Both sides of the limits, against the oracle.
 import numpy as np
 import pytest
 
-from paper_2506_01986_amd import synth
+import oracle
+from paper_2506_01986_amd import runner, synth
 
-from tests.test_gpu_parity import edge_cfg, run_parity, torch_cuda  # noqa: F401
+from tests.test_gpu_parity import close, edge_cfg, run_parity, torch_cuda  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
@@ -35,3 +36,19 @@ def test_batches(torch_cuda, name):  # noqa: F811
     trees = [synth.random_tree(rng, int(rng.integers(1, nodes + 1))) for _ in range(B)]
     cfg = edge_cfg(B=B, n_q=n_q, n_kv=n_kv, hidden=32, vocab=256)
     run_parity(torch_cuda, synth.make(cfg, trees=trees, lens=L), label=name)
+
+
+@pytest.mark.parametrize("head_dim", [32, 64, 128])
+def test_fp32_overflowed_scores(torch_cuda, head_dim):  # noqa: F811
+    """Keys whose score overflows to -inf get weight 0, also where a key slot of the kernel holds no other."""
+    cfg = edge_cfg(dtype="fp32", B=2, n_q=4, n_kv=2, head_dim=head_dim, hidden=32, vocab=256)
+    wl = synth.make(cfg, trees=[synth.chain_tree(1), synth.t16()], lens=[13, 60])
+    wl.q = (np.abs(wl.q) + 1).astype(np.float32)
+    for b in range(2):
+        wl.pool_k[:, int(wl.seq_base[b]):int(wl.seq_base[b]) + 13] = -3e38
+    step = runner.VerifyStep(wl)
+    step.tree_attn()
+    torch_cuda.cuda.synchronize()
+    got = step.out.double().cpu().numpy()
+    ref = oracle.tree_attn(wl.q, wl.pool_k, wl.pool_v, wl.node_off, wl.parent, wl.lens, wl.seq_base, cfg.n_kv)
+    assert close(got.reshape(ref.shape), ref, "fp32") <= 0
