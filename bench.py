@@ -43,7 +43,7 @@ HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, published
 MFMA_PEAK_TFLOPS = {"bf16": 2500.0, "fp32": 157.3}   # MI355X dense matrix bf16 / fp32 vector, published
 METRIC = "verified tree tokens/sec per verify step; achieved HBM GB/s vs peak"
 # Kernels each stage launches through the C ABI (for matching rocprofv3 traces).
-STAGE_KERNELS = {"medusa_topk": ["head_logits_packed", "topk_rows"],
+STAGE_KERNELS = {"medusa_topk": ["head_gemm", "topk_rows"],
                  "tree_attn": ["tree_attn_bf16", "tree_attn_combine"],
                  "accept": ["row_argbest_all", "accept_walk"], "kv_compact": ["kv_compact_kernel"],
                  "accept_compact": ["row_argbest_all", "accept_walk_compact"]}
@@ -59,9 +59,9 @@ def stage_kernels(stage, dtype):
 # internal.h): a counter summary is used only while their hash is unchanged.
 STAGE_SOURCES = {"medusa_topk": ["medusa_topk.hip"], "tree_attn": ["tree_attn.hip"],
                  "accept": ["accept.hip"], "kv_compact": ["kv_compact.hip", "compact_rows.h"],
-                 "accept_compact": ["accept.hip", "compact_rows.h"], "head_logits_packed": ["medusa_topk.hip"]}
+                 "accept_compact": ["accept.hip", "compact_rows.h"], "head_gemm": ["medusa_topk.hip"]}
 # The dominant kernel of a stage, timed by itself for the roofline entry.
-DOMINANT_KERNEL = {"medusa_topk": "head_logits_packed"}
+DOMINANT_KERNEL = {"medusa_topk": "head_gemm"}
 
 
 def source_sha(stage):
@@ -584,14 +584,14 @@ def main():
                             "GBps": round(byts["accept"] / (tt * 1e-3) / 1e9, 1),
                             "hbm_frac": round(byts["accept"] / (tt * 1e-3) / 1e9 / HBM_PEAK_GBS, 4)}
     dom = max(names, key=lambda n: st[n]["ms"])
-    if DOMINANT_KERNEL.get(dom) == "head_logits_packed" and step.head_layout == sm.HEADS_PACKED:
+    if DOMINANT_KERNEL.get(dom) == "head_gemm" and step.head_layout == sm.HEADS_PACKED:
         print("[bench] projection kernel alone", file=sys.stderr, flush=True)
         kms, kbytes = projection_kernel(torch, sm, step, cfg, args.steps)
         kgbs = kbytes / (kms * 1e-3) / 1e9
-        roofline = {"bound": "hbm", "kernel": "head_logits_packed", "stage": dom, "achieved": round(kgbs, 1),
+        roofline = {"bound": "hbm", "kernel": "head_gemm", "stage": dom, "achieved": round(kgbs, 1),
                     "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(kgbs / HBM_PEAK_GBS, 4),
-                    "traffic": measured_traffic("head_logits_packed", cfg.name), "algorithmic_bytes": kbytes,
-                    "ms": round(kms, 5), "source_sha256_16": source_sha("head_logits_packed")}
+                    "traffic": measured_traffic("head_gemm", cfg.name), "algorithmic_bytes": kbytes,
+                    "ms": round(kms, 5), "source_sha256_16": source_sha("head_gemm")}
     elif dom == "tree_attn" and cfg.dtype == "bf16":
         # attention above the ridge point (FLOP per algorithmic byte > 2.5 PFLOP/s / 8 TB/s): matrix-core bound
         roofline = {"bound": "mfma", "kernel": dom, "kernels": stage_kernels(dom, cfg.dtype), "achieved": st[dom]["TFLOPs"],

@@ -196,7 +196,8 @@ size_t specmemo_packed_heads_bytes(specmemo_dtype dt, int32_t n_heads, int32_t v
  * head_dim <= 128 and head_dim % 4 == 0.  n_q % n_kv == 0.  Rows of the slab
  * past L_b + N_b are never read.  ws: at least
  * specmemo_workspace_bytes(SPECMEMO_WS_ATTN, ...) bytes (the partial results
- * of KV ranges split across work items; with more than 32 sequences also the
+ * of KV ranges split across work items; with more sequences than the kernel
+ * arguments describe, 32 or, with KV heads a multiple of eight, 120, also the
  * per-sequence descriptors and the work map of the single launch, written
  * into ws by the call's own kernels; may be 0). */
 int specmemo_tree_attn(specmemo_dtype dt, const specmemo_trees *t, const specmemo_kv *kv,

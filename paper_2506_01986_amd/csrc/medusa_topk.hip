@@ -9,7 +9,7 @@
 // HBM-bound for any batch of a verify step, so waves stream 64 vocabulary rows
 // each with 16-byte loads and contract them on the 16x16x32 bf16 matrix cores
 // (batch padded to 16s: the padding costs matrix-core time that is far below
-// the load time).  Packed heads: head_gemm; row-major ones: head_logits_bf16.
+// the load time).  Packed heads: head_gemm; row-major ones: head_rows.
 #include <type_traits>
 
 #include "device.h"
