@@ -39,8 +39,7 @@ __device__ __forceinline__ uint32_t bf16x2_keys(uint32_t w) {
   return w ^ (__builtin_bit_cast(uint32_t, sign) | 0x80008000u);
 }
 
-// 16-byte loads per thread: rows of at most kNT U chunks stay in registers
-constexpr int kArgU = 8, kArgULong = 16;
+constexpr int kArgU = 8;                          // 16-byte loads per thread
 
 // A logit row as whole 16-byte chunks at 16-byte aligned addresses and, where
 // the vocabulary keeps rows from starting or ending on one, up to 14 single
@@ -71,16 +70,15 @@ struct RowParts {
   }
 };
 
-// Arg-best of a bf16 row of at most kNT U chunks, in two steps over the same
+// Arg-best of a bf16 row of at most kNT kArgU chunks, in two steps over the same
 // registers: the row's largest key (one packed 16-bit maximum per two values),
 // then the lowest id holding it, searched only by the threads whose own maximum
 // is that key.  NaN rows are not valid input.
-template <int U>
 __device__ void row_argbest_bf16(const RowParts<1> &r, const uint16_t *row, uint32_t *sk, float &out_v, int &out_i) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  uint4 w[U];
+  uint4 w[kArgU];
 #pragma unroll
-  for (int u = 0; u < U; ++u) {
+  for (int u = 0; u < kArgU; ++u) {
     const int c = u * kNT + tid;
     w[u] = c < r.nch ? r.p[c] : uint4{~0u, ~0u, ~0u, ~0u};   // keys of 0, below every value
   }
@@ -88,7 +86,7 @@ __device__ void row_argbest_bf16(const RowParts<1> &r, const uint16_t *row, uint
   const uint32_t single = tid < r.singles ? bf16x2_keys(row[sid]) & 0xFFFFu : 0u;
   u16x2_t mx = __builtin_bit_cast(u16x2_t, single);
 #pragma unroll
-  for (int u = 0; u < U; ++u) {
+  for (int u = 0; u < kArgU; ++u) {
     w[u].x = bf16x2_keys(w[u].x);
     w[u].y = bf16x2_keys(w[u].y);
     w[u].z = bf16x2_keys(w[u].z);
@@ -108,7 +106,7 @@ __device__ void row_argbest_bf16(const RowParts<1> &r, const uint16_t *row, uint
   uint32_t cand = 0xFFFFFFFFu;
   if (tk == k || tk == alt) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
+    for (int u = 0; u < kArgU; ++u) {
       const uint32_t ws[4] = {w[u].x, w[u].y, w[u].z, w[u].w};
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
@@ -134,15 +132,15 @@ __device__ void row_argbest_bf16(const RowParts<1> &r, const uint16_t *row, uint
 
 // Arg-best (largest value, lowest id) of one logit row; result in every thread.
 // Rows that fit no registers, and fp32 rows, compare (value, id) pairs.
-template <int DT, int U>
+template <int DT>
 __device__ void row_argbest(const void *logits, int64_t row, int vocab, float *sv, int *si,
                             float &out_v, int &out_i) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const RowParts<DT> r(logits, row, vocab);
   constexpr int V = RowParts<DT>::kVpc;
   if constexpr (DT == 1)
-    if (r.nch <= kNT * U) {
-      row_argbest_bf16<U>(r, static_cast<const uint16_t *>(logits) + row * vocab, reinterpret_cast<uint32_t *>(si), out_v, out_i);
+    if (r.nch <= kNT * kArgU) {
+      row_argbest_bf16(r, static_cast<const uint16_t *>(logits) + row * vocab, reinterpret_cast<uint32_t *>(si), out_v, out_i);
       return;
     }
   float bv = -INFINITY;
@@ -156,15 +154,15 @@ __device__ void row_argbest(const void *logits, int64_t row, int vocab, float *s
     }
   }
   // All of this thread's loads of a pass are issued before any compare.
-  for (int c0 = 0; c0 < r.nch; c0 += kNT * U) {
-    uint4 w[U];
+  for (int c0 = 0; c0 < r.nch; c0 += kNT * kArgU) {
+    uint4 w[kArgU];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
+    for (int u = 0; u < kArgU; ++u) {
       const int c = c0 + u * kNT + tid;
       w[u] = c < r.nch ? r.p[c] : uint4{0u, 0u, 0u, 0u};
     }
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
+    for (int u = 0; u < kArgU; ++u) {
       const int c = c0 + u * kNT + tid;
 #pragma unroll
       for (int e = 0; e < V; ++e) {
@@ -198,13 +196,13 @@ __device__ void row_argbest(const void *logits, int64_t row, int vocab, float *s
 
 // Greedy mode, pass 1: the arg-best token of every node's logit row, all rows
 // at once (the walk of pass 2 then has no dependent row loads).
-template <int DT, int U>
+template <int DT>
 __global__ __launch_bounds__(kNT) void row_argbest_all(AcceptArgs a) {
   __shared__ float sv[kWaves];
   __shared__ int si[kWaves];
   float v;
   int tok;
-  row_argbest<DT, U>(a.logits, blockIdx.x, a.vocab, sv, si, v, tok);
+  row_argbest<DT>(a.logits, blockIdx.x, a.vocab, sv, si, v, tok);
   if (threadIdx.x == 0) a.best[blockIdx.x] = tok;
 }
 
@@ -347,12 +345,12 @@ __device__ __forceinline__ void stat_term(float z, float c, float M, float &s, f
   t = fmaf(e, d, t);
 }
 
-// A row of at most kNT U chunks stays in registers, all loads in flight; a
+// A row of at most kNT kArgU chunks stays in registers, all loads in flight; a
 // longer one is read twice.
 // The lowest id of the maximum is searched only by threads
 // that hold it: two compares and a select per value less (2160 rows of 32000 with
 // the rest of the typical call: 48.4 -> 47.8 us, this pass 31 us, 4.5 TB/s).
-template <int DT, int U>
+template <int DT>
 __global__ __launch_bounds__(kNT) void row_softmax_stats(AcceptArgs a) {
   __shared__ float red[3 * kWaves];
   const int u = blockIdx.x, tid = threadIdx.x;
@@ -361,11 +359,11 @@ __global__ __launch_bounds__(kNT) void row_softmax_stats(AcceptArgs a) {
   constexpr int V = RowParts<DT>::kVpc;
   const int sid = r.single_id(tid);
   const float single = tid < r.singles ? ld<DT>(a.logits, (int64_t)u * a.vocab + sid) : -INFINITY;
-  uint4 w[U];
+  uint4 w[kArgU];
   auto load = [&](int c0) {
     const uint32_t fill = DT == 0 ? 0xFF800000u : 0xFF80FF80u;   // -inf
 #pragma unroll
-    for (int k = 0; k < U; ++k) {
+    for (int k = 0; k < kArgU; ++k) {
       const int ch = c0 + k * kNT + tid;
       w[k] = ch < r.nch ? r.p[ch] : uint4{fill, fill, fill, fill};
     }
@@ -373,7 +371,7 @@ __global__ __launch_bounds__(kNT) void row_softmax_stats(AcceptArgs a) {
   float mz = single;
   auto maxima = [&] {
 #pragma unroll
-    for (int k = 0; k < U; ++k)
+    for (int k = 0; k < kArgU; ++k)
 #pragma unroll
       for (int e = 0; e < V; e += 2) mz = fmaxf(mz, fmaxf(RowParts<DT>::value(w[k], e), RowParts<DT>::value(w[k], e + 1)));
   };
@@ -381,13 +379,13 @@ __global__ __launch_bounds__(kNT) void row_softmax_stats(AcceptArgs a) {
   uint32_t cand = 0xFFFFFFFFu, first = 0xFFFFFFFFu;
   auto sums = [&](int c0) {
 #pragma unroll
-    for (int k = 0; k < U; ++k)
+    for (int k = 0; k < kArgU; ++k)
       if (c0 + k * kNT + tid < r.nch)
 #pragma unroll
         for (int e = 0; e < V; ++e) stat_term(RowParts<DT>::value(w[k], e), c, M, s, t);
     if (mz == zmax) {                              // the few threads that hold the maximum look for its lowest id
 #pragma unroll
-      for (int k = U - 1; k >= 0; --k) {
+      for (int k = kArgU - 1; k >= 0; --k) {
         const int ch = c0 + k * kNT + tid;
         if (ch < r.nch)
 #pragma unroll
@@ -399,7 +397,7 @@ __global__ __launch_bounds__(kNT) void row_softmax_stats(AcceptArgs a) {
   };
   load(0);
   maxima();
-  for (int c0 = kNT * U; c0 < r.nch; c0 += kNT * U) {
+  for (int c0 = kNT * kArgU; c0 < r.nch; c0 += kNT * kArgU) {
     load(c0);
     maxima();
   }
@@ -409,10 +407,10 @@ __global__ __launch_bounds__(kNT) void row_softmax_stats(AcceptArgs a) {
     stat_term(single, c, M, s, t);
     if (single == zmax) cand = (uint32_t)sid;
   }
-  if (r.nch <= kNT * U) {
+  if (r.nch <= kNT * kArgU) {
     sums(0);
   } else {
-    for (int c0 = 0; c0 < r.nch; c0 += kNT * U) {
+    for (int c0 = 0; c0 < r.nch; c0 += kNT * kArgU) {
       load(c0);
       sums(c0);
     }
@@ -689,11 +687,16 @@ hipError_t launch_sample_next(int dt, const SampleArgs &a, int B, uint64_t *word
 }
 
 hipError_t launch_accept_rows(int dt, const AcceptArgs &a, int total_nodes, hipStream_t st) {
-  const bool longer = a.vocab > kNT * kArgU * (dt == 1 ? 8 : 4);   // chunks of the shorter form
-  auto kern = a.mode == 0 ? (dt == 0 ? row_argbest_all<0, kArgU> : longer ? row_argbest_all<1, kArgULong> : row_argbest_all<1, kArgU>)
-              : dt == 1   ? (longer ? row_softmax_stats<1, kArgULong> : row_softmax_stats<1, kArgU>)
-                          : (longer ? row_softmax_stats<0, kArgULong> : row_softmax_stats<0, kArgU>);
-  hipLaunchKernelGGL(kern, dim3(total_nodes), dim3(kNT), 0, st, a);
+  if (a.mode == 0) {
+    if (dt == 1)
+      hipLaunchKernelGGL(row_argbest_all<1>, dim3(total_nodes), dim3(kNT), 0, st, a);
+    else
+      hipLaunchKernelGGL(row_argbest_all<0>, dim3(total_nodes), dim3(kNT), 0, st, a);
+  } else if (dt == 1) {
+    hipLaunchKernelGGL(row_softmax_stats<1>, dim3(total_nodes), dim3(kNT), 0, st, a);
+  } else {
+    hipLaunchKernelGGL(row_softmax_stats<0>, dim3(total_nodes), dim3(kNT), 0, st, a);
+  }
   return hipGetLastError();
 }
 

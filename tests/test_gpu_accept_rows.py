@@ -1,7 +1,7 @@
 """GPU: the row passes of the acceptance on rows of any length and alignment.
 
 Rows are read in 16-byte chunks at aligned addresses and up to 14 single values
-around them; they stay in registers up to 4096 or 8192 chunks.  48 rows of an odd
+around them; they stay in registers up to 4096 chunks.  48 rows of an odd
 vocabulary meet every alignment.  Arg-best tokens are exact; lse and entropy are
 fp32 sums of positive terms over a row (tree-wise below 100 terms in sequence,
 2^-24 each, on values of about 12, and the exponentials' few ulp): within 2e-5.
@@ -19,7 +19,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "fp32"])
-@pytest.mark.parametrize("vocab", [7, 9, 30, 1001, 4094, 8197, 16384, 16393, 32003, 32761, 32783, 40009, 65549])
+@pytest.mark.parametrize("vocab", [7, 9, 30, 1001, 4094, 8197, 16384, 16393, 32003, 32761, 32783, 40009])
 def test_ragged_rows(torch_cuda, vocab, dtype):  # noqa: F811
     import torch
     from paper_2506_01986_amd import specmemo as sm
