@@ -66,7 +66,8 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void head_gemm(
   constexpr int RG = NW / KS;                    // row groups per block
   constexpr int kPer = kShare ? NB * KS * KC / NW : 1;   // 16-byte pieces of a chunk per thread
   constexpr int kBuf = kShare ? KS * KC * NB * 64 : 0;        // entries of a states buffer
-  constexpr int kRed = KS > 1 ? NW * 4 * 64 : 0; // a batch tile of every wave, for the ranges' sums
+  constexpr int kTile = NW * 4 * 64;             // a batch tile of every wave, for the ranges' sums
+  constexpr int kRed = KS == 1 ? 0 : NB == 1 ? kTile : 2 * kTile;
   __shared__ u32x4_t hsh[2 * kBuf > kRed ? 2 * kBuf : kRed > 0 ? kRed : 1];
   // the wave's number, made uniform for the compiler: its bases then stay in scalar registers
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -190,27 +191,40 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void head_gemm(
         }
       }
   }
-  if constexpr (KS > 1) {                        // the ranges' sums, added in range order; one batch tile at a time
+  // The ranges' sums, added in range order, one batch tile at a time (two
+  // buffers in turn).  Wave n % KS of a row group finishes tile n: with one wave
+  // for all, the rest waited for its stores (residual blocks of 512 columns, 2
+  // heads, 128 states, 8 tiles a block: 36.5 us, of which 30 were this).
+  if constexpr (KS > 1) {
     f32x4 *red = reinterpret_cast<f32x4 *>(hsh);
+    __syncthreads();                             // every wave is past its reads of the states
 #pragma unroll
     for (int n = 0; n < NB; ++n) {
+      f32x4 *buf = red + (n & 1) * kTile;
+      const bool mine = n % KS == sl;
+      if (!mine)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) buf[(wave * 4 + t) * 64 + lane] = acc[n][t];
       __syncthreads();
-      if (sl > 0)
+      if (mine)
 #pragma unroll
-        for (int t = 0; t < 4; ++t) red[(wave * 4 + t) * 64 + lane] = acc[n][t];
-      __syncthreads();
-      if (sl == 0)
+        for (int t = 0; t < 4; ++t) {
+          const f32x4 own = acc[n][t];
+          f32x4 v = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int w = 1; w < KS; ++w)
-#pragma unroll
-          for (int t = 0; t < 4; ++t) acc[n][t] += red[((wave + w) * 4 + t) * 64 + lane];
+          for (int w = 0; w < KS; ++w) {
+            const f32x4 part = w == sl ? own : buf[((wave - sl + w) * 4 + t) * 64 + lane];
+            v = w == 0 ? part : v + part;
+          }
+          acc[n][t] = v;
+        }
     }
-    if (sl > 0) return;
   }
   if (!active) return;
   // C layout: lane holds column (batch) lane&15, rows 4*(lane>>4) + 0..3 of each tile.
 #pragma unroll
   for (int n = 0; n < NB; ++n) {
+    if (KS > 1 && n % KS != sl) continue;
     const int b = b0 + 16 * n + r16;
     if constexpr (EPI == 0) {
       float m = -INFINITY;
@@ -762,11 +776,23 @@ hipError_t launch_gemm(const void *h, int64_t h_head_stride, const void *w, cons
                          int B, int hidden, int rows, int n_heads, float *gmax, hipStream_t st) {
   // batch tiles of a block: the fewest of 1, 2, 4, 6, 8 that hold the batch (past 128 states, groups of 128);
   // the shared states are addressed with 32 bits from a group's first row, which 2^24 columns could exceed
-  auto kern = B <= 16 || hidden >= 1 << 24 ? launch_gemm_nb<EPI, 1>
-              : B <= 32                          ? launch_gemm_nb<EPI, 2>
-              : B <= 64                          ? launch_gemm_nb<EPI, 4>
-              : B <= 96                          ? launch_gemm_nb<EPI, 6>
-                                                 : launch_gemm_nb<EPI, 8>;
+  int nb = B <= 16 || hidden >= 1 << 24 ? 1 : B <= 32 ? 2 : B <= 64 ? 4 : B <= 96 ? 6 : 8;
+  // Few row groups leave units idle, and the weights are small: the batch is spread over blocks with as few tiles
+  // as still make one round (residual blocks of 512 columns, 2 heads, 128 states: 6.4 us at 1, 7.7 at 2, 9.2 at 4,
+  // 15.6 at 8 tiles; of 4096: 54 us at 1, which makes 4 rounds, 26.5 at 4, 47 at 8).  Past one round short rows,
+  // whose epilogue outweighs the weights, stay at 4 (2048 columns, 5 heads, 128 states: 24.5 us at 4, 29.8 at 8;
+  // 4096 columns, 189 groups, 100 states: 42.8 and 39.8 us).
+  const int64_t groups = (int64_t)packed_row_groups(rows) * n_heads;
+  if (groups <= kCus) {
+    for (int n = 1; n <= 4; n *= 2)
+      if (n < nb && groups * ((B + 16 * n - 1) / (16 * n)) <= kCus) nb = n;
+    if (nb > 4 && hidden <= 2048) nb = 4;
+  }
+  auto kern = nb == 1   ? launch_gemm_nb<EPI, 1>
+              : nb == 2 ? launch_gemm_nb<EPI, 2>
+              : nb == 4 ? launch_gemm_nb<EPI, 4>
+              : nb == 6 ? launch_gemm_nb<EPI, 6>
+                        : launch_gemm_nb<EPI, 8>;
   kern(h, h_head_stride, w, bias, z, hout, B, hidden, rows, n_heads, gmax, st);
   return hipGetLastError();
 }

@@ -14,6 +14,7 @@ import pytest
 
 import oracle
 from paper_2506_01986_amd import synth
+from tests.gpu_time import graph_us
 
 pytestmark = pytest.mark.gpu
 
@@ -95,3 +96,26 @@ def test_resblock_forms(gpu, n_heads, B, hidden):
         # |SiLU'| <= 1.1; the activation itself adds a few ulp of y
         bound = 1.1 * (hidden + 8) * 2.0 ** -24 * size + 2.0 ** -20 * (1 + y.abs()) + 2.0 ** -8 * ref.abs()
         assert float(((out[i].double() - ref).abs() - bound).max()) <= 0
+
+
+@pytest.mark.parametrize("n_heads,hidden,few,many,at_most", [(2, 512, 16, 128, 2.0), (2, 4096, 64, 128, 1.6)])
+def test_residual_blocks_spread_the_batch(gpu, n_heads, hidden, few, many, at_most):
+    """Few row groups: more states go to more blocks, not to more work of one wave each."""
+    torch, sm, dev = gpu
+    us = []
+    for B in (few, many):
+        h, b = (torch.zeros(n, hidden, dtype=torch.bfloat16, device="cuda") for n in (B, n_heads))
+        w = torch.zeros(sm.packed_heads_bytes(sm.BF16, n_heads, hidden, hidden), dtype=torch.uint8, device="cuda")
+        out = torch.empty(n_heads, B, hidden, dtype=torch.bfloat16, device="cuda")
+        us.append(graph_us(torch, lambda: sm.medusa_resblock(sm.BF16, B, hidden, n_heads, h, w, b, out)))
+    assert us[1] <= at_most * us[0], us
+
+
+def test_small_heads_spread_the_batch(gpu):
+    torch, sm, dev = gpu
+    n_heads, vocab, hidden, us = 2, 50, 1000, []
+    w = torch.zeros(sm.packed_heads_bytes(sm.BF16, n_heads, vocab, hidden), dtype=torch.uint8, device="cuda")
+    for B in (16, 128):
+        h, z = torch.zeros(B, hidden, dtype=torch.bfloat16, device="cuda"), torch.empty(B, n_heads, vocab, device="cuda")
+        us.append(graph_us(torch, lambda: sm.head_logits(sm.BF16, B, hidden, vocab, n_heads, h, w, z, sm.HEADS_PACKED)))
+    assert us[1] <= 2.0 * us[0], us
