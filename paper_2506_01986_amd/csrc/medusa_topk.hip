@@ -169,28 +169,35 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void head_gemm(
     group(t0, std::false_type{});
   }
   // The range's last steps, and in the last range hidden % 32 columns more,
-  // four at a time: states straight from memory, zero past hidden.
+  // four, two or one at a time: states straight from memory, zero past hidden.
   const int n_all = n_mine + (sl == KS - 1 ? nS - nF : 0);
-  for (int s0 = n_main; s0 < n_all; s0 += 4) {
-    uint4 at[4][4];
+  auto rest = [&](int s0, auto count) {
+    constexpr int C = decltype(count)::value;
+    uint4 at[C][4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int s = min(s0 + u, n_all - 1), st = s < n_mine ? s_begin + s : nF;
+    for (int u = 0; u < C; ++u) {
+      const int st = s0 + u < n_mine ? s_begin + s0 + u : nF;
 #pragma unroll
       for (int t = 0; t < 4; ++t) at[u][t] = ld16_stream(wp + ((int64_t)(st - s_begin) * 4 + t) * 64 + lane);
     }
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
-      if (s0 + u < n_all) {
-        const int k = 32 * (s0 + u < n_mine ? s_begin + s0 + u : nF) + 8 * kq;
+    for (int u = 0; u < C; ++u) {
+      const int k = 32 * (s0 + u < n_mine ? s_begin + s0 + u : nF) + 8 * kq;
 #pragma unroll
-        for (int n = 0; n < NB; ++n) {
-          const int b = b0 + 16 * n + r16;
-          const bool in = b < B && k < hidden;
-          contract(at[u], __builtin_bit_cast(bf16x8, ld16_or_zero(in, hbase + (int64_t)(in ? b : 0) * hidden + (in ? k : 0))), n);
-        }
+      for (int n = 0; n < NB; ++n) {
+        const int b = b0 + 16 * n + r16;
+        const bool in = b < B && k < hidden;
+        contract(at[u], __builtin_bit_cast(bf16x8, ld16_or_zero(in, hbase + (int64_t)(in ? b : 0) * hidden + (in ? k : 0))), n);
       }
+    }
+  };
+  int s0 = n_main;
+  for (; s0 + 4 <= n_all; s0 += 4) rest(s0, std::integral_constant<int, 4>{});
+  if (s0 + 2 <= n_all) {
+    rest(s0, std::integral_constant<int, 2>{});
+    s0 += 2;
   }
+  if (s0 < n_all) rest(s0, std::integral_constant<int, 1>{});
   // The ranges' sums, added in range order, one batch tile at a time (two
   // buffers in turn).  Wave n % KS of a row group finishes tile n: with one wave
   // for all, the rest waited for its stores (residual blocks of 512 columns, 2
