@@ -749,7 +749,12 @@ constexpr int kCus = 256;   // compute units: each holds one 8-wave block or two
 // one batch tile the waves share nothing, and a nearly full round is 1 to 3%
 // faster in 4-wave blocks (1940 groups x 7800: 295 against 297 us; 2000 x 4096:
 // 153 against 161 us), a full one with the weights in bursts (2000 x 8192: 307
-// against 317 us; 1940 groups: 299 against 295 us).
+// against 317 us; 1940 groups: 299 against 295 us); 4 groups a block also go in
+// 4-wave blocks (640 groups x 8192, 10 states: 105 us, 113 in split 8-wave
+// ones).  Two tiles share states, and only a round that is full of short rows is
+// faster in 4-wave blocks (2000 groups, 17 states: x 1024 44 against 54 us, x 4096
+// 157 against 165, x 5120 194 against 193; 1940 x 4096 152 and 154; 1500 x 4096
+// 126 and 116).
 template <int EPI, int NB>
 void launch_gemm_nb(const void *h, int64_t h_head_stride, const void *w, const void *bias, float *z, void *hout,
                       int B, int hidden, int rows, int n_heads, float *gmax, hipStream_t st) {
@@ -762,16 +767,20 @@ void launch_gemm_nb(const void *h, int64_t h_head_stride, const void *w, const v
   };
   auto blocks = [&](int groups) { return (int64_t)((nG + groups - 1) / groups) * n_heads; };
   const int64_t rounds = (blocks(8) + kCus - 1) / kCus;
+  const bool full = blocks(8) * 100 >= rounds * kCus * 97;
   if (blocks(1) <= kCus) {
     go(head_gemm<4, NB, 4, (NB <= 4 ? 2 : 1), EPI>, 4, 1);
   } else if (blocks(2) <= kCus) {
     if constexpr (NB >= 6) go(head_gemm<8, NB, 4, (NB == 6 ? 2 : 1), EPI>, 8, 2);
     else go(head_gemm<4, NB, 2, 4, EPI>, 4, 2);
   } else if (blocks(4) <= kCus) {
-    go(head_gemm<8, NB, 2, (NB >= 6 ? 2 : 4), EPI>, 8, 4);
-  } else if (NB == 1 ? blocks(8) * 8 <= kCus * 7 : rounds == 1 || blocks(8) * 10 >= rounds * kCus * 9) {
+    if constexpr (NB == 1) go(head_gemm<4, 1, 1, 4, EPI>, 4, 4);
+    else go(head_gemm<8, NB, 2, (NB >= 6 ? 2 : 4), EPI>, 8, 4);
+  } else if (NB == 1                        ? blocks(8) * 8 <= kCus * 7
+             : NB == 2 && hidden <= 4096    ? !full && (rounds == 1 || blocks(8) * 10 >= rounds * kCus * 9)
+                                            : rounds == 1 || blocks(8) * 10 >= rounds * kCus * 9) {
     go(head_gemm<8, NB, 1, 4, EPI>, 8, 8);
-  } else if (NB == 1 && blocks(8) * 100 >= rounds * kCus * 97) {
+  } else if (NB == 1 && full) {
     if constexpr (NB == 1) go(head_gemm<4, 1, 1, 4, EPI, true>, 4, 4);
   } else {
     go(head_gemm<4, NB, 1, 4, EPI>, 4, 4);
