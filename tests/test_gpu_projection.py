@@ -111,11 +111,14 @@ def test_residual_blocks_spread_the_batch(gpu, n_heads, hidden, few, many, at_mo
     assert us[1] <= at_most * us[0], us
 
 
-def test_small_heads_spread_the_batch(gpu):
+@pytest.mark.parametrize("layout", ["packed", "rowmajor"])
+def test_small_heads_spread_the_batch(gpu, layout):
     torch, sm, dev = gpu
     n_heads, vocab, hidden, us = 2, 50, 1000, []
-    w = torch.zeros(sm.packed_heads_bytes(sm.BF16, n_heads, vocab, hidden), dtype=torch.uint8, device="cuda")
+    nb = sm.packed_heads_bytes(sm.BF16, n_heads, vocab, hidden)        # more than the row-major heads
+    w = torch.zeros(nb, dtype=torch.uint8, device="cuda")
     for B in (16, 128):
         h, z = torch.zeros(B, hidden, dtype=torch.bfloat16, device="cuda"), torch.empty(B, n_heads, vocab, device="cuda")
-        us.append(graph_us(torch, lambda: sm.head_logits(sm.BF16, B, hidden, vocab, n_heads, h, w, z, sm.HEADS_PACKED)))
+        us.append(graph_us(torch, lambda: sm.head_logits(sm.BF16, B, hidden, vocab, n_heads, h, w, z,
+                                                         sm.HEADS_PACKED if layout == "packed" else sm.HEADS_ROWMAJOR)))
     assert us[1] <= 2.0 * us[0], us
