@@ -10,6 +10,8 @@
 // has no dependent row loads, only one token per node crosses to it.  Typical
 // mode needs every node's softmax statistics: one block per row computes
 // them, then one block per sequence evaluates the edges and picks the path.
+#include <type_traits>
+
 #include "compact_rows.h"
 #include "device.h"
 #include "internal.h"
@@ -45,6 +47,8 @@ constexpr int kArgU = 8;                          // 16-byte loads per thread
 // the vocabulary keeps rows from starting or ending on one, up to 14 single
 // values: `head` of them before the chunks, the others after.  Value e of chunk c
 // has id head + kVpc c + e; single value t (one thread each) has single_id(t).
+// A row of at most kNT values is all single values (40 x 64 bf16 rows of 50:
+// 13.9 us in chunks, 6.6 us as single values, greedy).
 // Both row passes are bound by memory (a row's loads are its whole chain), which
 // 2-byte loads left idle: 24 x 64 rows of 32003 bf16 values, the whole greedy call
 // 52.0 -> 21.1 us, the typical one 115 -> 29.5 us; of 39999 values 62.6 -> 29.7 and
@@ -56,7 +60,7 @@ struct RowParts {
   int head, nch, singles;
   __device__ __forceinline__ RowParts(const void *logits, int64_t row, int vocab) {   // logits: 16-byte aligned
     const int64_t base = row * vocab;
-    head = min((int)(-base & (kVpc - 1)), vocab);
+    head = vocab <= kNT ? vocab : (int)(-base & (kVpc - 1));
     nch = (vocab - head) / kVpc;
     singles = vocab - nch * kVpc;
     p = reinterpret_cast<const uint4 *>(static_cast<const uint8_t *>(logits) + (base + head) * (16 / kVpc));
@@ -70,15 +74,28 @@ struct RowParts {
   }
 };
 
-// Arg-best of a bf16 row of at most kNT kArgU chunks, in two steps over the same
+// f with the number of chunks a thread holds of a row of at most kNT kArgU, as a
+// constant: work for chunks that a short row lacks is half of its pass (10 x 64
+// bf16 rows of 4000, greedy: 8.6 us with it, 5.2 without).
+template <class F>
+__device__ __forceinline__ void with_chunks(int nch, F f) {
+  if (nch == 0) f(std::integral_constant<int, 0>{});
+  else if (nch <= kNT) f(std::integral_constant<int, 1>{});
+  else if (nch <= 2 * kNT) f(std::integral_constant<int, 2>{});
+  else if (nch <= 4 * kNT) f(std::integral_constant<int, 4>{});
+  else f(std::integral_constant<int, kArgU>{});
+}
+
+// Arg-best of a bf16 row of at most kNT U chunks, in two steps over the same
 // registers: the row's largest key (one packed 16-bit maximum per two values),
 // then the lowest id holding it, searched only by the threads whose own maximum
 // is that key.  NaN rows are not valid input.
+template <int U>
 __device__ void row_argbest_bf16(const RowParts<1> &r, const uint16_t *row, uint32_t *sk, float &out_v, int &out_i) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  uint4 w[kArgU];
+  uint4 w[U > 0 ? U : 1];
 #pragma unroll
-  for (int u = 0; u < kArgU; ++u) {
+  for (int u = 0; u < U; ++u) {
     const int c = u * kNT + tid;
     w[u] = c < r.nch ? r.p[c] : uint4{~0u, ~0u, ~0u, ~0u};   // keys of 0, below every value
   }
@@ -86,7 +103,7 @@ __device__ void row_argbest_bf16(const RowParts<1> &r, const uint16_t *row, uint
   const uint32_t single = tid < r.singles ? bf16x2_keys(row[sid]) & 0xFFFFu : 0u;
   u16x2_t mx = __builtin_bit_cast(u16x2_t, single);
 #pragma unroll
-  for (int u = 0; u < kArgU; ++u) {
+  for (int u = 0; u < U; ++u) {
     w[u].x = bf16x2_keys(w[u].x);
     w[u].y = bf16x2_keys(w[u].y);
     w[u].z = bf16x2_keys(w[u].z);
@@ -106,7 +123,7 @@ __device__ void row_argbest_bf16(const RowParts<1> &r, const uint16_t *row, uint
   uint32_t cand = 0xFFFFFFFFu;
   if (tk == k || tk == alt) {
 #pragma unroll
-    for (int u = 0; u < kArgU; ++u) {
+    for (int u = 0; u < U; ++u) {
       const uint32_t ws[4] = {w[u].x, w[u].y, w[u].z, w[u].w};
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
@@ -131,7 +148,7 @@ __device__ void row_argbest_bf16(const RowParts<1> &r, const uint16_t *row, uint
 }
 
 // Arg-best (largest value, lowest id) of one logit row; result in every thread.
-// Rows that fit no registers, and fp32 rows, compare (value, id) pairs.
+// bf16 rows that fit no registers, and fp32 rows, compare (value, id) pairs.
 template <int DT>
 __device__ void row_argbest(const void *logits, int64_t row, int vocab, float *sv, int *si,
                             float &out_v, int &out_i) {
@@ -140,7 +157,10 @@ __device__ void row_argbest(const void *logits, int64_t row, int vocab, float *s
   constexpr int V = RowParts<DT>::kVpc;
   if constexpr (DT == 1)
     if (r.nch <= kNT * kArgU) {
-      row_argbest_bf16(r, static_cast<const uint16_t *>(logits) + row * vocab, reinterpret_cast<uint32_t *>(si), out_v, out_i);
+      with_chunks(r.nch, [&](auto u) {
+        row_argbest_bf16<decltype(u)::value>(r, static_cast<const uint16_t *>(logits) + row * vocab,
+                                             reinterpret_cast<uint32_t *>(si), out_v, out_i);
+      });
       return;
     }
   float bv = -INFINITY;
@@ -153,25 +173,31 @@ __device__ void row_argbest(const void *logits, int64_t row, int vocab, float *s
       bi = v;
     }
   }
-  // All of this thread's loads of a pass are issued before any compare.
-  for (int c0 = 0; c0 < r.nch; c0 += kNT * kArgU) {
-    uint4 w[kArgU];
+  auto compare = [&](const uint4 &w, int c) {
 #pragma unroll
-    for (int u = 0; u < kArgU; ++u) {
-      const int c = c0 + u * kNT + tid;
-      w[u] = c < r.nch ? r.p[c] : uint4{0u, 0u, 0u, 0u};
+    for (int e = 0; e < V; ++e) {
+      const float x = RowParts<DT>::value(w, e);
+      const int v = r.head + V * c + e;
+      if (better(x, v, bv, bi)) {
+        bv = x;
+        bi = v;
+      }
     }
+  };
+  if constexpr (DT == 0) {   // batches of loads are slower here (10 x 64 rows of 32000: 18.5 us, 16.1 us one by one)
+    for (int c = tid; c < r.nch; c += kNT) compare(r.p[c], c);
+  } else {                   // all of this thread's loads of a pass are issued before any compare
+    for (int c0 = 0; c0 < r.nch; c0 += kNT * kArgU) {
+      uint4 w[kArgU];
 #pragma unroll
-    for (int u = 0; u < kArgU; ++u) {
-      const int c = c0 + u * kNT + tid;
+      for (int u = 0; u < kArgU; ++u) {
+        const int c = c0 + u * kNT + tid;
+        w[u] = c < r.nch ? r.p[c] : uint4{0u, 0u, 0u, 0u};
+      }
 #pragma unroll
-      for (int e = 0; e < V; ++e) {
-        const float x = RowParts<DT>::value(w[u], e);
-        const int v = r.head + V * c + e;
-        if (c < r.nch && better(x, v, bv, bi)) {
-          bv = x;
-          bi = v;
-        }
+      for (int u = 0; u < kArgU; ++u) {
+        const int c = c0 + u * kNT + tid;
+        if (c < r.nch) compare(w[u], c);
       }
     }
   }
@@ -345,25 +371,22 @@ __device__ __forceinline__ void stat_term(float z, float c, float M, float &s, f
   t = fmaf(e, d, t);
 }
 
-// A row of at most kNT kArgU chunks stays in registers, all loads in flight; a
-// longer one is read twice.
-// The lowest id of the maximum is searched only by threads
-// that hold it: two compares and a select per value less (2160 rows of 32000 with
-// the rest of the typical call: 48.4 -> 47.8 us, this pass 31 us, 4.5 TB/s).
-template <int DT>
-__global__ __launch_bounds__(kNT) void row_softmax_stats(AcceptArgs a) {
-  __shared__ float red[3 * kWaves];
-  const int u = blockIdx.x, tid = threadIdx.x;
-  const float c = a.inv_temp * 1.4426950408889634f;   // y = z c
-  const RowParts<DT> r(a.logits, u, a.vocab);
+// A row of at most kNT kArgU chunks stays in registers (U of them a thread), all
+// loads in flight; a longer one (LONG) is read twice.  The lowest id of the maximum
+// is searched only by threads that hold it: two compares and a select per value
+// less (2160 rows of 32000 with the rest of the typical call: 48.4 -> 47.8 us, this
+// pass 31 us, 4.5 TB/s).
+template <int DT, int U, bool LONG>
+__device__ __forceinline__ void softmax_stats(const AcceptArgs &a, int u, const RowParts<DT> &r, float *red) {
   constexpr int V = RowParts<DT>::kVpc;
-  const int sid = r.single_id(tid);
+  const int tid = threadIdx.x, sid = r.single_id(tid);
+  const float c = a.inv_temp * 1.4426950408889634f;   // y = z c
   const float single = tid < r.singles ? ld<DT>(a.logits, (int64_t)u * a.vocab + sid) : -INFINITY;
-  uint4 w[kArgU];
+  uint4 w[U > 0 ? U : 1];
   auto load = [&](int c0) {
     const uint32_t fill = DT == 0 ? 0xFF800000u : 0xFF80FF80u;   // -inf
 #pragma unroll
-    for (int k = 0; k < kArgU; ++k) {
+    for (int k = 0; k < U; ++k) {
       const int ch = c0 + k * kNT + tid;
       w[k] = ch < r.nch ? r.p[ch] : uint4{fill, fill, fill, fill};
     }
@@ -371,7 +394,7 @@ __global__ __launch_bounds__(kNT) void row_softmax_stats(AcceptArgs a) {
   float mz = single;
   auto maxima = [&] {
 #pragma unroll
-    for (int k = 0; k < kArgU; ++k)
+    for (int k = 0; k < U; ++k)
 #pragma unroll
       for (int e = 0; e < V; e += 2) mz = fmaxf(mz, fmaxf(RowParts<DT>::value(w[k], e), RowParts<DT>::value(w[k], e + 1)));
   };
@@ -379,13 +402,13 @@ __global__ __launch_bounds__(kNT) void row_softmax_stats(AcceptArgs a) {
   uint32_t cand = 0xFFFFFFFFu, first = 0xFFFFFFFFu;
   auto sums = [&](int c0) {
 #pragma unroll
-    for (int k = 0; k < kArgU; ++k)
+    for (int k = 0; k < U; ++k)
       if (c0 + k * kNT + tid < r.nch)
 #pragma unroll
         for (int e = 0; e < V; ++e) stat_term(RowParts<DT>::value(w[k], e), c, M, s, t);
     if (mz == zmax) {                              // the few threads that hold the maximum look for its lowest id
 #pragma unroll
-      for (int k = kArgU - 1; k >= 0; --k) {
+      for (int k = U - 1; k >= 0; --k) {
         const int ch = c0 + k * kNT + tid;
         if (ch < r.nch)
 #pragma unroll
@@ -397,25 +420,37 @@ __global__ __launch_bounds__(kNT) void row_softmax_stats(AcceptArgs a) {
   };
   load(0);
   maxima();
-  for (int c0 = kNT * kArgU; c0 < r.nch; c0 += kNT * kArgU) {
-    load(c0);
-    maxima();
-  }
+  if constexpr (LONG)
+    for (int c0 = kNT * U; c0 < r.nch; c0 += kNT * U) {
+      load(c0);
+      maxima();
+    }
   zmax = block_max(mz, red);
   M = zmax * c;
   if (tid < r.singles) {
     stat_term(single, c, M, s, t);
     if (single == zmax) cand = (uint32_t)sid;
   }
-  if (r.nch <= kNT * kArgU) {
-    sums(0);
-  } else {
-    for (int c0 = 0; c0 < r.nch; c0 += kNT * kArgU) {
+  if constexpr (LONG) {
+    for (int c0 = 0; c0 < r.nch; c0 += kNT * U) {
       load(c0);
       sums(c0);
     }
+  } else {
+    sums(0);
   }
   finish_stats(a, u, M, s, t, cand, red);
+}
+
+template <int DT>
+__global__ __launch_bounds__(kNT) void row_softmax_stats(AcceptArgs a) {
+  __shared__ float red[3 * kWaves];
+  const int u = blockIdx.x;
+  const RowParts<DT> r(a.logits, u, a.vocab);
+  if (r.nch <= kNT * kArgU)
+    with_chunks(r.nch, [&](auto n) { softmax_stats<DT, decltype(n)::value, false>(a, u, r, red); });
+  else
+    softmax_stats<DT, kArgU, true>(a, u, r, red);
 }
 
 // Typical mode, pass 2, by one block: the edges of sequence b's tree (one
