@@ -699,11 +699,15 @@ __global__ __launch_bounds__(4 * RB) void tree_attn_combine(AttnArgs a) {
 // batches in turn, and each key slot runs its own online softmax; the slots'
 // (m, l, o) meet in LDS at the end.  16 nodes, 4 heads, 128 keys: 35 us with
 // one wave per (node, head), one key per load and a six-step reduction each.
+// W: waves of a block, one where the launch's longest sequence has at most
+// kF32Short committed keys and three waves would only wait (8 x 64 nodes, 32
+// heads, 4 keys of 128 columns: 40.5 us at 4 waves, 17.5 us at 1; 16 keys: 42.2 and 23.1).
 constexpr int kF32Batch = 4;
+constexpr int kF32Short = 16;
 
-template <int LPK>
-__global__ __launch_bounds__(256) void tree_attn_f32(AttnArgs a, int node_begin) {
-  constexpr int KPW = 64 / LPK, P = 4 * KPW;       // keys per load and wave, key slots of the block
+template <int LPK, int W>
+__global__ __launch_bounds__(64 * W) void tree_attn_f32(AttnArgs a, int node_begin) {
+  constexpr int KPW = 64 / LPK, P = W * KPW;       // keys per load and wave, key slots of the block
   __shared__ int par[kMaxNodes], path[kMaxPath];
   __shared__ int path_len;
   __shared__ float pm[P], pl[P];
@@ -713,7 +717,7 @@ __global__ __launch_bounds__(256) void tree_attn_f32(AttnArgs a, int node_begin)
   const int s = find_seq(a.nseq, lane < kMaxSeqPerLaunch ? a.seq[lane].node0 : 0, gnode);
   const AttnSeq &S = a.seq[s];
   const int n = gnode - S.node0, kvh = hq / a.group, d = a.head_dim, N = S.N, L = S.L;
-  if (tid < N) par[tid] = a.parent[S.node0 + tid];
+  for (int i = tid; i < N; i += 64 * W) par[i] = a.parent[S.node0 + i];
   const int sl = lane / LPK, c = 4 * (lane % LPK), slot = wave * KPW + sl;
   const bool in = c < d;                           // head_dim % 4 == 0
   const int cc = in ? c : 0;
@@ -780,17 +784,16 @@ __global__ __launch_bounds__(256) void tree_attn_f32(AttnArgs a, int node_begin)
     path_len = len;
   }
   __syncthreads();
-  {
-    const int len = path_len;
+  const int len = path_len;
+  for (int i0 = 0; i0 < len; i0 += P * kF32Batch) {   // four waves: one batch
     int row[kF32Batch];
     bool use[kF32Batch];
 #pragma unroll
     for (int u = 0; u < kF32Batch; ++u) {
-      const int i = u * P + slot;
+      const int i = i0 + u * P + slot;
       use[u] = i < len;
       row[u] = L + path[i < len ? i : 0];
     }
-    static_assert(kF32Batch * P >= kMaxPath, "one batch takes the longest path");
     batch(row, use);
   }
   if (lane % LPK == 0) {
@@ -799,17 +802,18 @@ __global__ __launch_bounds__(256) void tree_attn_f32(AttnArgs a, int node_begin)
   }
   *reinterpret_cast<f32x4 *>(&po[slot][c]) = o;
   __syncthreads();
-  if (tid >= d) return;
-  float M = -INFINITY, lsum = 0.f, acc = 0.f;
+  for (int e = tid; e < d; e += 64 * W) {
+    float M = -INFINITY, lsum = 0.f, acc = 0.f;
 #pragma unroll
-  for (int i = 0; i < P; ++i) M = fmaxf(M, pm[i]); // finite: the node's own row is visible
+    for (int i = 0; i < P; ++i) M = fmaxf(M, pm[i]); // finite: the node's own row is visible
 #pragma unroll
-  for (int i = 0; i < P; ++i) {
-    const float w = expf(pm[i] - M);               // a slot without a visible key: 0
-    lsum = fmaf(pl[i], w, lsum);
-    acc = fmaf(po[i][tid], w, acc);
+    for (int i = 0; i < P; ++i) {
+      const float w = expf(pm[i] - M);               // a slot without a visible key: 0
+      lsum = fmaf(pl[i], w, lsum);
+      acc = fmaf(po[i][e], w, acc);
+    }
+    static_cast<float *>(a.out)[((int64_t)gnode * a.n_q + hq) * d + e] = acc / lsum;
   }
-  static_cast<float *>(a.out)[((int64_t)gnode * a.n_q + hq) * d + tid] = acc / lsum;
 }
 
 }  // namespace
@@ -866,8 +870,12 @@ hipError_t attn_static_scratch(void **ptr) {
 }
 
 hipError_t launch_tree_attn_f32(const AttnArgs &a, int node_begin, int node_count, hipStream_t st) {
-  auto kern = a.head_dim <= 32 ? tree_attn_f32<8> : a.head_dim <= 64 ? tree_attn_f32<16> : tree_attn_f32<32>;
-  hipLaunchKernelGGL(kern, dim3(a.n_q, node_count), dim3(256), 0, st, a, node_begin);
+  int longest = 0;
+  for (int i = 0; i < a.nseq; ++i) longest = a.seq[i].L > longest ? a.seq[i].L : longest;
+  const int w = longest <= kF32Short ? 1 : 4;
+  auto kern = w == 1 ? (a.head_dim <= 32 ? tree_attn_f32<8, 1> : a.head_dim <= 64 ? tree_attn_f32<16, 1> : tree_attn_f32<32, 1>)
+                     : (a.head_dim <= 32 ? tree_attn_f32<8, 4> : a.head_dim <= 64 ? tree_attn_f32<16, 4> : tree_attn_f32<32, 4>);
+  hipLaunchKernelGGL(kern, dim3(a.n_q, node_count), dim3(64 * w), 0, st, a, node_begin);
   return hipGetLastError();
 }
 

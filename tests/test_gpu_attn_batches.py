@@ -8,6 +8,7 @@ import pytest
 
 import oracle
 from paper_2506_01986_amd import runner, synth
+from tests.gpu_time import graph_us
 
 from tests.test_gpu_parity import close, edge_cfg, run_parity, torch_cuda  # noqa: F401
 
@@ -52,3 +53,28 @@ def test_fp32_overflowed_scores(torch_cuda, head_dim):  # noqa: F811
     got = step.out.double().cpu().numpy()
     ref = oracle.tree_attn(wl.q, wl.pool_k, wl.pool_v, wl.node_off, wl.parent, wl.lens, wl.seq_base, cfg.n_kv)
     assert close(got.reshape(ref.shape), ref, "fp32") <= 0
+
+
+@pytest.mark.parametrize("longest", [0, 16, 17, 65])
+@pytest.mark.parametrize("head_dim", [4, 32, 36, 64, 96, 128])
+def test_fp32_short_contexts(torch_cuda, head_dim, longest):  # noqa: F811
+    """One wave a block up to 16 committed keys, four beyond; root paths of up to 16 nodes."""
+    cfg = edge_cfg(dtype="fp32", B=4, n_q=6, n_kv=2, head_dim=head_dim, hidden=32, vocab=256, n_heads=15, topk=(2,) * 15)
+    rng = np.random.default_rng(head_dim)
+    trees = [synth.chain_tree(16), synth.random_tree(rng, 128), synth.chain_tree(1), synth.t16()]
+    wl = synth.make(cfg, trees=trees, lens=[longest, longest // 2, max(longest - 1, 0), min(longest, 1)])
+    step = runner.VerifyStep(wl)
+    step.tree_attn()
+    torch_cuda.cuda.synchronize()
+    ref = oracle.tree_attn(wl.q, wl.pool_k, wl.pool_v, wl.node_off, wl.parent, wl.lens, wl.seq_base, cfg.n_kv)
+    assert close(step.out.double().cpu().numpy().reshape(ref.shape), ref, "fp32") <= 0
+
+
+def test_fp32_short_contexts_cost_less(torch_cuda):  # noqa: F811
+    """4 committed keys against 64: waves that would only wait are not launched."""
+    us = []
+    for L in (4, 64):
+        cfg = edge_cfg(dtype="fp32", B=8, n_q=32, n_kv=8, hidden=32, vocab=256)
+        step = runner.VerifyStep(synth.make(cfg, trees=[synth.t64()] * 8, lens=[L] * 8))
+        us.append(graph_us(torch_cuda, step.tree_attn))
+    assert us[0] <= 0.4 * us[1], us
