@@ -348,3 +348,25 @@ def test_copied_mirrors_have_their_own_addresses():
         for other in (copy.copy(obj), copy.deepcopy(obj), pickle.loads(pickle.dumps(obj))):
             assert other._addresses() == tuple(getattr(other, n).ctypes.data for n in obj._MIRRORS)
         assert copy.deepcopy(obj)._addresses() != obj._addresses()
+
+
+def test_resized_and_unwritable_mirrors_are_followed():
+    """A mirror may be resized in place, put in the object's dict, read-only, strided or empty."""
+    pool = sm.KVPool(np.zeros((1, 8, 128), np.float32), FAKE, FAKE, [0], [8], [3])
+    pool.struct()
+    for _ in range(4):
+        pool.seq_len_h.resize(100_000, refcheck=False)       # realloc moves it
+        assert pool.struct().seq_len_h == pool.seq_len_h.ctypes.data
+        pool.seq_len_h.resize(1, refcheck=False)
+        assert pool.struct().seq_len_h == pool.seq_len_h.ctypes.data
+    pool.__dict__["seq_cap_h"] = np.full(1, 8, np.int32)
+    assert pool.struct().seq_cap_h == pool.seq_cap_h.ctypes.data
+    fixed = np.full(4, 5, np.int32)
+    fixed.setflags(write=False)
+    for mirror in (fixed, np.arange(8, dtype=np.int32)[::2], np.zeros(0, np.int32)):
+        pool.seq_len_h = mirror
+        assert pool.struct().seq_len_h == mirror.ctypes.data
+    for other in (bytearray(4), [3]):                        # not arrays: refused as ever
+        pool.seq_len_h = other
+        with pytest.raises(AttributeError):
+            pool.struct()
