@@ -3,7 +3,9 @@
 Packed weights: the launch picks the batch tiles of a block (1, 2, 4, 6 or 8 of 16 states) from
 the batch, and the row groups and k ranges of a block from the number of row
 groups; the k steps divide into pipelined groups, the ranges' rests and a last
-partial step.  Sizes sit on both sides of every such line.  References are fp64;
+partial step.  Sizes sit on both sides of every such line, and a second list
+(test_projection_forms.py) reaches every form with several pipelined groups.
+References are fp64;
 |error| <= (hidden + 8) 2^-24 sum |w h| (fp32 summation in any order), and for
 the residual blocks half a bf16 step more (of eight significant bits: 2^-8 of
 the value).
@@ -15,6 +17,7 @@ import pytest
 import oracle
 from paper_2506_01986_amd import synth
 from tests.gpu_time import graph_us
+from tests.test_projection_forms import FORM_CASES, packed_form
 
 pytestmark = pytest.mark.gpu
 
@@ -95,6 +98,103 @@ def test_resblock_forms(gpu, n_heads, B, hidden):
         size = hd.double().abs() @ wd[i].double().abs().t() + bd[i].double().abs()
         # |SiLU'| <= 1.1; the activation itself adds a few ulp of y
         bound = 1.1 * (hidden + 8) * 2.0 ** -24 * size + 2.0 ** -20 * (1 + y.abs()) + 2.0 ** -8 * ref.abs()
+        assert float(((out[i].double() - ref).abs() - bound).max()) <= 0
+
+
+def device_normal(torch, shape, std, seed):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    return torch.empty(shape, dtype=torch.bfloat16, device="cuda").normal_(0.0, std, generator=g)
+
+
+def check_heads(torch, sm, n_heads, B, vocab, hidden, packed):
+    h, w = device_normal(torch, (B, hidden), 1.0, 1), device_normal(torch, (n_heads, vocab, hidden), 0.05, 2)
+    k = 10
+    z = torch.full((B, n_heads, vocab), float("nan"), device="cuda")
+    ids = torch.full((B, n_heads, k), -1, dtype=torch.int32, device="cuda")
+    vals = torch.empty((B, n_heads, k), device="cuda")
+    zero = np.zeros(B, np.int32)
+    tr = sm.Trees(np.arange(B + 1), np.full(B, -1), zero, zero, device="cuda")       # single-node trees
+    tok, root = (torch.zeros(B, dtype=torch.int32, device="cuda") for _ in range(2))
+    nb = sm.workspace_bytes(sm.WS_TOPK, sm.BF16, tr, None, n_heads, vocab)
+    ws = torch.empty(nb, dtype=torch.uint8, device="cuda")
+    sm.medusa_topk(sm.BF16, tr, hidden, vocab, n_heads, [k] * n_heads, h, pack(torch, sm, w) if packed else w, root,
+                   ids, tok, logits_out=z, topk_vals=vals, ws=ws, ws_bytes=nb,
+                   head_layout=sm.HEADS_PACKED if packed else sm.HEADS_ROWMAJOR)
+    hd = h.double()
+    for i in range(n_heads):
+        w64 = w[i].double().t()
+        err = (z[:, i].double() - hd @ w64).abs() - (hidden + 8) * 2.0 ** -24 * (hd.abs() @ w64.abs())
+        assert float(err.max()) <= 0 and bool(torch.isfinite(z[:, i]).all())
+    # the group maxima lead to the largest of these logits
+    assert torch.equal(vals, torch.topk(z, k, dim=2).values)
+    assert torch.equal(z.gather(2, ids.long()), vals)
+
+
+@pytest.mark.parametrize("n_heads,B,vocab,hidden", FORM_CASES)
+def test_every_packed_form(gpu, n_heads, B, vocab, hidden):
+    torch, sm, dev = gpu
+    check_heads(torch, sm, n_heads, B, vocab, hidden, True)
+
+
+# row-major: 256 blocks of 128 rows, so that 17, 33 and 65 states make 2, 4 and 8 tiles; chunks that go round
+# the rings of 4, 3, 3 and 2, and a rest; then few rows, the batch over several blocks
+@pytest.mark.parametrize("n_heads,B,vocab,hidden", [
+    (4, 16, 8101, 1160), (4, 20, 8101, 904), (4, 33, 8101, 1160), (4, 64, 8192, 904), (4, 65, 8101, 648),
+    (4, 128, 8130, 1160), (4, 200, 8101, 136), (2, 100, 4003, 648), (1, 129, 300, 904)])
+def test_every_rowmajor_form(gpu, n_heads, B, vocab, hidden):
+    torch, sm, dev = gpu
+    check_heads(torch, sm, n_heads, B, vocab, hidden, False)
+
+
+@pytest.mark.parametrize("n_heads,hidden", [(4, 2104), (10, 2104), (15, 3208)])
+@pytest.mark.parametrize("B", [10, 20, 40, 70, 100])
+def test_residual_block_forms_in_groups(gpu, n_heads, hidden, B):
+    """One, two and four row groups a block, 1 to 8 batch tiles, several pipelined groups."""
+    torch, sm, dev = gpu
+    assert packed_form(B, n_heads, hidden, hidden)[1] >= 3
+    h, w, b = (device_normal(torch, s, std, i) for i, (s, std) in enumerate(
+        [((B, hidden), 1.0), ((n_heads, hidden, hidden), 0.05), ((n_heads, hidden), 0.5)]))
+    out = torch.full((n_heads, B, hidden), float("nan"), dtype=torch.bfloat16, device="cuda")
+    sm.medusa_resblock(sm.BF16, B, hidden, n_heads, h, pack(torch, sm, w), b, out)
+    hd = h.double()
+    for i in range(n_heads):
+        w64 = w[i].double().t()
+        y = hd @ w64 + b[i].double()
+        ref = hd + y * torch.sigmoid(y)
+        bound = 1.1 * (hidden + 8) * 2.0 ** -24 * (hd.abs() @ w64.abs() + b[i].double().abs()) + \
+            2.0 ** -20 * (1 + y.abs()) + 2.0 ** -8 * ref.abs()
+        assert float(((out[i].double() - ref).abs() - bound).max()) <= 0
+
+
+@pytest.mark.parametrize("hidden", [40, 264, 640, 648, 1000, 1032])
+@pytest.mark.parametrize("B", [1, 2, 3, 5, 32])
+def test_fp32_forms(gpu, B, hidden):
+    """fp32 heads and residual blocks: one, two and four states a wave, short rows and several strides, row counts
+    that are no multiple of a wave's four or a block's sixteen."""
+    torch, sm, dev = gpu
+    g = torch.Generator(device="cuda")
+    g.manual_seed(B * hidden)
+
+    def normal(*shape):
+        return torch.empty(shape, device="cuda").normal_(generator=g)
+    h, hs = normal(B, hidden), (2 * hidden + 40) * 2.0 ** -24
+    hd = h.double()
+    for vocab in (1, 50, 333):
+        w = normal(3, vocab, hidden)
+        z = torch.full((B, 3, vocab), float("nan"), device="cuda")
+        sm.head_logits(sm.FP32, B, hidden, vocab, 3, h, w, z)
+        for i in range(3):
+            w64 = w[i].double().t()
+            assert float(((z[:, i].double() - hd @ w64).abs() - hs * (hd.abs() @ w64.abs())).max()) <= 0
+    w, b = normal(2, hidden, hidden), normal(2, hidden)
+    out = torch.full((2, B, hidden), float("nan"), device="cuda")
+    sm.medusa_resblock(sm.FP32, B, hidden, 2, h, w, b, out, w1_layout=sm.HEADS_ROWMAJOR)
+    for i in range(2):
+        w64 = w[i].double().t()
+        y = hd @ w64 + b[i].double()
+        ref = hd + y * torch.sigmoid(y)
+        bound = 1.1 * hs * (hd.abs() @ w64.abs() + b[i].double().abs()) + 2.0 ** -20 * (1 + y.abs() + ref.abs())
         assert float(((out[i].double() - ref).abs() - bound).max()) <= 0
 
 
