@@ -10,6 +10,7 @@ import oracle
 from paper_2506_01986_amd import runner, synth
 from tests.gpu_time import graph_us
 
+from tests.test_gpu_padded import padded_workload, run_padded_parity
 from tests.test_gpu_parity import close, edge_cfg, run_parity, torch_cuda  # noqa: F401
 
 pytestmark = pytest.mark.gpu
@@ -37,6 +38,28 @@ def test_batches(torch_cuda, name):  # noqa: F811
     trees = [synth.random_tree(rng, int(rng.integers(1, nodes + 1))) for _ in range(B)]
     cfg = edge_cfg(B=B, n_q=n_q, n_kv=n_kv, hidden=32, vocab=256)
     run_parity(torch_cuda, synth.make(cfg, trees=trees, lens=L), label=name)
+
+
+# sequences, query heads, KV heads, most tree nodes, tokens held, runs of pads (whole chunks of the first sequences)
+PADDED = {
+    "b40_mha_few_rows": (40, 8, 8, 20, lens(40, 200, 40), {}),              # 64-row items, waves without rows
+    "b36_mha_split": (36, 16, 16, 12, lens(36, 120, 4000), {0: (900, 2200)}),
+    "b34_gqa_split": (34, 32, 8, 40, lens(34, 150, 5000, 60), {0: (1500, 3600), 1: (3, 10 ** 6)}),   # 128-row items
+    "b120": (120, 8, 8, 6, lens(120, 60, 500), {}),
+    "b121": (121, 8, 8, 6, lens(121, 60, 500), {}),                         # one more: the workspace table
+}
+
+
+@pytest.mark.parametrize("name", list(PADDED))
+def test_padded_batches(torch_cuda, name):  # noqa: F811
+    """The pad mask's words are found from the packed 32-bit bases, which are no multiples of 32 here."""
+    B, n_q, n_kv, nodes, held, runs = PADDED[name]
+    rng = np.random.default_rng(B)
+    cfg = edge_cfg(B=B, n_q=n_q, n_kv=n_kv, hidden=32, vocab=256)
+    trees = [synth.random_tree(rng, int(rng.integers(1, nodes + 1)), max_depth=4) for _ in range(B)]
+    wl, flags = padded_workload(cfg, trees, [x + 45 for x in held], 8, seed=B, pad_runs=runs)
+    assert len({int(x) % 32 for x in wl.seq_base}) > 8
+    run_padded_parity(torch_cuda, wl, flags, label=name)
 
 
 @pytest.mark.parametrize("head_dim", [32, 64, 128])
