@@ -39,6 +39,16 @@ int specmemo::ok() {
   return SPECMEMO_OK;
 }
 
+int specmemo::device_cus() {
+  int dev = 0, n = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) {
+    (void)hipGetLastError();
+    return 256;
+  }
+  return n;
+}
+
 namespace {
 
 bool al(const void *p, uintptr_t a) { return p != nullptr && (reinterpret_cast<uintptr_t>(p) % a) == 0; }
@@ -162,18 +172,6 @@ struct AttnPlan {
   std::vector<AttnItem> map, cmap;
   size_t map_off = 0, cmap_off = 0, part_off = 0;
 };
-
-// Compute units of the current device (256 on MI355X; also the fallback when no
-// device is visible, so that workspace sizes can be planned on a host).
-int device_cus() {
-  int dev = 0, n = 0;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) {
-    (void)hipGetLastError();
-    return 256;
-  }
-  return n;
-}
 
 // Chunks per sequence for one launch (sets s.nch and s.ch_len).  A work item
 // of sequence s covers about (L + N) / nch keys.  When the unsplit items fit

@@ -24,6 +24,10 @@ hipError_t upload_table(const void *src, size_t bytes, void *dst, hipStream_t st
 int fail(int code, const char *fmt, ...) __attribute__((format(printf, 2, 3)));
 int ok();
 
+// Compute units of the current device (256 on MI355X; also the fallback when no
+// device is visible, so that workspace sizes can be planned on a host).
+int device_cus();
+
 // ---- head projection + top-k -------------------------------------------------
 struct TopkArgs {
   const float *z;          // [B][n_heads][vocab] fp32 logits

@@ -735,8 +735,6 @@ __global__ __launch_bounds__(kTopkThreads) void topk_rows(TopkArgs a) {
 
 namespace {
 
-constexpr int kCus = 256;   // compute units: each holds one 8-wave block or two 4-wave blocks
-
 // Kernel form for NB batch tiles.  One round of blocks, one per compute unit,
 // streams best, so a block takes the fewest row groups (1, 2, 4 or 8) with
 // which the launch still is one.  With fewer it runs in more rounds (1128
@@ -765,20 +763,21 @@ void launch_gemm_nb(const void *h, int64_t h_head_stride, const void *w, const v
                        static_cast<const uint4 *>(w), static_cast<const uint16_t *>(bias), z,
                        static_cast<uint16_t *>(hout), B, hidden, rows, n_heads, nG, nS, gmax);
   };
+  const int64_t cus = device_cus();   // each holds one 8-wave block or two 4-wave blocks
   auto blocks = [&](int groups) { return (int64_t)((nG + groups - 1) / groups) * n_heads; };
-  const int64_t rounds = (blocks(8) + kCus - 1) / kCus;
-  const bool full = blocks(8) * 100 >= rounds * kCus * 97;
-  if (blocks(1) <= kCus) {
+  const int64_t rounds = (blocks(8) + cus - 1) / cus;
+  const bool full = blocks(8) * 100 >= rounds * cus * 97;
+  if (blocks(1) <= cus) {
     go(head_gemm<4, NB, 4, (NB <= 4 ? 2 : 1), EPI>, 4, 1);
-  } else if (blocks(2) <= kCus) {
+  } else if (blocks(2) <= cus) {
     if constexpr (NB >= 6) go(head_gemm<8, NB, 4, (NB == 6 ? 2 : 1), EPI>, 8, 2);
     else go(head_gemm<4, NB, 2, 4, EPI>, 4, 2);
-  } else if (blocks(4) <= kCus) {
+  } else if (blocks(4) <= cus) {
     if constexpr (NB == 1) go(head_gemm<4, 1, 1, 4, EPI>, 4, 4);
     else go(head_gemm<8, NB, 2, (NB >= 6 ? 2 : 4), EPI>, 8, 4);
-  } else if (NB == 1                        ? blocks(8) * 8 <= kCus * 7
-             : NB == 2 && hidden <= 4096    ? !full && (rounds == 1 || blocks(8) * 10 >= rounds * kCus * 9)
-                                            : rounds == 1 || blocks(8) * 10 >= rounds * kCus * 9) {
+  } else if (NB == 1                        ? blocks(8) * 8 <= cus * 7
+             : NB == 2 && hidden <= 4096    ? !full && (rounds == 1 || blocks(8) * 10 >= rounds * cus * 9)
+                                            : rounds == 1 || blocks(8) * 10 >= rounds * cus * 9) {
     go(head_gemm<8, NB, 1, 4, EPI>, 8, 8);
   } else if (NB == 1 && full) {
     if constexpr (NB == 1) go(head_gemm<4, 1, 1, 4, EPI, true>, 4, 4);
@@ -798,10 +797,10 @@ hipError_t launch_gemm(const void *h, int64_t h_head_stride, const void *w, cons
   // 15.6 at 8 tiles; of 4096: 54 us at 1, which makes 4 rounds, 26.5 at 4, 47 at 8).  Past one round short rows,
   // whose epilogue outweighs the weights, stay at 4 (2048 columns, 5 heads, 128 states: 24.5 us at 4, 29.8 at 8;
   // 4096 columns, 189 groups, 100 states: 42.8 and 39.8 us).
-  const int64_t groups = (int64_t)packed_row_groups(rows) * n_heads;
-  if (groups <= kCus) {
+  const int64_t groups = (int64_t)packed_row_groups(rows) * n_heads, cus = device_cus();
+  if (groups <= cus) {
     for (int n = 1; n <= 4; n *= 2)
-      if (n < nb && groups * ((B + 16 * n - 1) / (16 * n)) <= kCus) nb = n;
+      if (n < nb && groups * ((B + 16 * n - 1) / (16 * n)) <= cus) nb = n;
     if (nb > 4 && hidden <= 2048) nb = 4;
   }
   auto kern = nb == 1   ? launch_gemm_nb<EPI, 1>
@@ -837,9 +836,9 @@ hipError_t launch_head_logits(int dt, const void *h, int64_t h_head_stride, cons
     int nb = B <= 16 || hidden >= 1 << 24 ? 1 : B <= 32 ? 2 : B <= 64 ? 4 : 8;
     // A vocabulary that leaves units idle (one block a unit): as few tiles as still make one round (2 heads, 128
     // states, 50 x 1000: 5.8 us at 1 tile, 17.3 at 8; 4000 x 4096: 30.7 us at 1, two rounds, 19.4 at 2, 46.5 at 8).
-    const int64_t blocks = (int64_t)((vocab + 127) / 128) * n_heads;
+    const int64_t blocks = (int64_t)((vocab + 127) / 128) * n_heads, cus = device_cus();
     for (int n = 1; n <= 4; n *= 2)
-      if (n < nb && blocks * ((B + 16 * n - 1) / (16 * n)) <= kCus) nb = n;
+      if (n < nb && blocks * ((B + 16 * n - 1) / (16 * n)) <= cus) nb = n;
     const dim3 grid((vocab + 127) / 128, n_heads, (B + 16 * nb - 1) / (16 * nb));
     auto kern = nb == 1 ? head_rows<1, 4> : nb == 2 ? head_rows<2, 3> : nb == 4 ? head_rows<4, 3> : head_rows<8, 2>;
     hipLaunchKernelGGL(kern, grid, dim3(512), 0, st, static_cast<const uint16_t *>(h), h_head_stride,
