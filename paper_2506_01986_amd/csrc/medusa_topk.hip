@@ -32,8 +32,9 @@ __device__ __forceinline__ uint4 ld16_stream(const uint4 *p) {
 // Bound by the weight stream (HBM) up to 128 hidden states, so the weights are
 // read once for all of them: a wave keeps the accumulators of one 64-row group
 // x 16 NB states in registers and streams the group's 1 KB operand tiles.
-// 4 heads x 32000 x 8192: 10 states 307 us, 120 states 338 us (6.4 TB/s; 1345 us
-// when 32 states were the most that shared a stream).
+// 4 heads x 32000 x 8192, this kernel alone: 10 states 300 us (7.0 TB/s of
+// weights), 120 states 332 us (6.3 TB/s; 1345 us with top-k when 32 states were
+// the most that shared a stream).
 //
 // KS waves share a row group and split its k steps in contiguous ranges, whose
 // partial sums meet in LDS: see launch_gemm_nb for when.
@@ -291,7 +292,10 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void head_gemm(
 // (rows of 8192: 498 us without, 355 us with; of 5120: 215 and 217 us).
 // 4 heads, 4 states, 32003 x 5120: 268 -> 217 us; 10 states, 32000 x 8192: 402 ->
 // 355 us (5.9 TB/s); 16 states, 18001 x 5120: 283 -> 149 us; 40 states, 32000 x
-// 4096, one weight stream instead of two: 453 -> 196 us.  gmax: as in head_gemm.
+// 4096, one weight stream instead of two: 453 -> 196 us; 65 to 128 states (two
+// slots), 32003 x 5120: 937 to 1367 -> 327 to 364 us.  One block fills a unit, so a
+// last round that is nearly empty costs one: 33 states, 17001 x 7800 (532 blocks)
+// 275 us, 3.9 TB/s.  gmax: as in head_gemm.
 template <int NB, int SLOTS>
 __global__ __launch_bounds__(512, 2) void head_rows(const uint16_t *__restrict__ h, int64_t h_head_stride,
                                                     const uint8_t *__restrict__ W, float *__restrict__ z, int B,
@@ -747,7 +751,9 @@ namespace {
 // one batch tile the waves share nothing, and a nearly full round is 1 to 3%
 // faster in 4-wave blocks (1940 groups x 7800: 295 against 297 us; 2000 x 4096:
 // 153 against 161 us), a full one with the weights in bursts (2000 x 8192: 307
-// against 317 us; 1940 groups: 299 against 295 us); 4 groups a block also go in
+// against 317 us; 1940 groups: 299 against 295 us; columns below 1024 end before a
+// second burst: 2000 groups x 256, 1 state, 11.6 us in bursts, 10.6 without, x 512
+// 21.6 and 20.0, x 1024 41.0 and 43.6); 4 groups a block also go in
 // 4-wave blocks (640 groups x 8192, 10 states: 105 us, 113 in split 8-wave
 // ones).  Two tiles share states, and only a round that is full of short rows is
 // faster in 4-wave blocks (2000 groups, 17 states: x 1024 44 against 54 us, x 4096
@@ -779,7 +785,7 @@ void launch_gemm_nb(const void *h, int64_t h_head_stride, const void *w, const v
              : NB == 2 && hidden <= 4096    ? !full && (rounds == 1 || blocks(8) * 10 >= rounds * cus * 9)
                                             : rounds == 1 || blocks(8) * 10 >= rounds * cus * 9) {
     go(head_gemm<8, NB, 1, 4, EPI>, 8, 8);
-  } else if (NB == 1 && full) {
+  } else if (NB == 1 && full && hidden >= 1024) {
     if constexpr (NB == 1) go(head_gemm<4, 1, 1, 4, EPI, true>, 4, 4);
   } else {
     go(head_gemm<4, NB, 1, 4, EPI>, 4, 4);

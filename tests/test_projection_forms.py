@@ -29,7 +29,7 @@ def packed_form(B, n_heads, rows, hidden):
     elif (blocks[8] * 8 <= CUS * 7 if nb == 1 else wide and not (full and nb == 2 and hidden <= 4096)):
         f = (8, nb, 1, 4, False)
     else:
-        f = (4, nb, 1, 4, nb == 1 and full)
+        f = (4, nb, 1, 4, nb == 1 and full and hidden >= 1024)
     pre = 8 if f[4] else PRE
     return f, max(0, nF - (f[2] - 1) * cdiv(nF, f[2])) // pre
 
@@ -41,7 +41,8 @@ FORMS = [
     (4, 12790, 1064, (16, 31, 33, 65, 97)),         # four (one tile: one range)
     (4, 19150, 520, (3, 32, 64, 90, 120)),          # eight
     (4, 33250, 424, (16, 20, 50, 81, 113)),         # eight would leave a short last round
-    (4, 32000, 1000, (10, 24)),                     # a full round: bursts, 4-wave blocks
+    (4, 32000, 1032, (10, 24)),                     # a full round: bursts, 4-wave blocks
+    (4, 32000, 424, (10,)),                         # the same of short columns: no bursts
     (4, 29650, 424, (10, 24)),                      # nearly full
     (2, 650, 2104, (40, 100, 200)),                 # few groups: the batch over several blocks
     (5, 1000, 2040, (64, 200)),
