@@ -492,8 +492,9 @@ int specmemo_plan_tree_sizes(int32_t B, const int32_t *seq_len_h, const int32_t 
  *                       fp32 logits, none when logits_out is given; bf16 also
  *                       the maxima of 64-row groups, which let the top-k pass
  *                       read only the groups that can hold a
- *                       top-k value; without room for them it scans every
- *                       logit, with the same result).
+ *                       top-k value; without room for them, and on rows of
+ *                       fewer than 2 k groups, it scans every logit, with the
+ *                       same result).
  *   SPECMEMO_WS_ATTN:   kv required; n_q_or_heads = n_q; vocab ignored.
  *   SPECMEMO_WS_ACCEPT: kv ignored; n_q_or_heads = accept mode; vocab ignored
  *                       (with more than 32 sequences it includes the

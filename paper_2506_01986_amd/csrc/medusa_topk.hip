@@ -33,7 +33,7 @@ __device__ __forceinline__ uint4 ld16_stream(const uint4 *p) {
 // read once for all of them: a wave keeps the accumulators of one 64-row group
 // x 16 NB states in registers and streams the group's 1 KB operand tiles.
 // 4 heads x 32000 x 8192, this kernel alone: 10 states 300 us (7.0 TB/s of
-// weights), 120 states 332 us (6.3 TB/s; 1345 us with top-k when 32 states were
+// weights), 120 states 332 to 341 us (6.2 TB/s; 1345 us with top-k when 32 states were
 // the most that shared a stream).
 //
 // KS waves share a row group and split its k steps in contiguous ranges, whose
