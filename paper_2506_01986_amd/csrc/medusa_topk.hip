@@ -753,9 +753,11 @@ namespace {
 // 153 against 161 us), a full one with the weights in bursts (2000 x 8192: 307
 // against 317 us; 1940 groups: 299 against 295 us; columns below 1024 end before a
 // second burst: 2000 groups x 256, 1 state, 11.6 us in bursts, 10.6 without, x 512
-// 21.6 and 20.0, x 1024 41.0 and 43.6); 4 groups a block also go in
-// 4-wave blocks (640 groups x 8192, 10 states: 105 us, 113 in split 8-wave
-// ones).  Two tiles share states, and only a round that is full of short rows is
+// 21.6 and 20.0, x 1024 41.0 and 43.6); 4 groups a block of residual blocks also go
+// in 4-wave blocks (640 groups x 8192, 10 states: 105 us, 113 in split 8-wave ones;
+// heads stay split, whose sums of two ranges lie nearer to 64 bits: 576 groups x
+// 8192 4.0e-7, in one range 5.8e-7, at 109 and 102 us).
+// Two tiles share states, and only a round that is full of short rows is
 // faster in 4-wave blocks (2000 groups, 17 states: x 1024 44 against 54 us, x 4096
 // 157 against 165, x 5120 194 against 193; 1940 x 4096 152 and 154; 1500 x 4096
 // 126 and 116).
@@ -779,7 +781,7 @@ void launch_gemm_nb(const void *h, int64_t h_head_stride, const void *w, const v
     if constexpr (NB >= 6) go(head_gemm<8, NB, 4, (NB == 6 ? 2 : 1), EPI>, 8, 2);
     else go(head_gemm<4, NB, 2, 4, EPI>, 4, 2);
   } else if (blocks(4) <= cus) {
-    if constexpr (NB == 1) go(head_gemm<4, 1, 1, 4, EPI>, 4, 4);
+    if constexpr (NB == 1 && EPI == 1) go(head_gemm<4, 1, 1, 4, EPI>, 4, 4);
     else go(head_gemm<8, NB, 2, (NB >= 6 ? 2 : 4), EPI>, 8, 4);
   } else if (NB == 1                        ? blocks(8) * 8 <= cus * 7
              : NB == 2 && hidden <= 4096    ? !full && (rounds == 1 || blocks(8) * 10 >= rounds * cus * 9)
