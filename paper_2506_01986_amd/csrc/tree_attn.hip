@@ -699,9 +699,12 @@ __global__ __launch_bounds__(4 * RB) void tree_attn_combine(AttnArgs a) {
 // batches in turn, and each key slot runs its own online softmax; the slots'
 // (m, l, o) meet in LDS at the end.  16 nodes, 4 heads, 128 keys: 35 us with
 // one wave per (node, head), one key per load and a six-step reduction each.
-// W: waves of a block, one where the launch's longest sequence has at most
-// kF32Short committed keys and three waves would only wait (8 x 64 nodes, 32
-// heads, 4 keys of 128 columns: 40.5 us at 4 waves, 17.5 us at 1; 16 keys: 42.2 and 23.1).
+// W: waves of a block, fewer where the launch's longest sequence has at most
+// kF32Short committed keys and the others would only wait (8 x 64 nodes, 32
+// heads, 128 columns: 4 keys 40.5 us at 4 waves, 17.5 us at 1; 16 keys 42.2 at 4,
+// 29.0 at 2).  Past 64 columns a wave has two key slots, and 9 to 16 keys take
+// two waves: chains of more keys a slot lie further from 64 bits (16 keys:
+// 1.21e-7 at 1 wave, 1.17e-7 at 4 and at 2).
 constexpr int kF32Batch = 4;
 constexpr int kF32Short = 16;
 
@@ -785,7 +788,7 @@ __global__ __launch_bounds__(64 * W) void tree_attn_f32(AttnArgs a, int node_beg
   }
   __syncthreads();
   const int len = path_len;
-  for (int i0 = 0; i0 < len; i0 += P * kF32Batch) {   // four waves: one batch
+  for (int i0 = 0; i0 < len; i0 += P * kF32Batch) {   // four slots and more: one batch
     int row[kF32Batch];
     bool use[kF32Batch];
 #pragma unroll
@@ -872,9 +875,10 @@ hipError_t attn_static_scratch(void **ptr) {
 hipError_t launch_tree_attn_f32(const AttnArgs &a, int node_begin, int node_count, hipStream_t st) {
   int longest = 0;
   for (int i = 0; i < a.nseq; ++i) longest = a.seq[i].L > longest ? a.seq[i].L : longest;
-  const int w = longest <= kF32Short ? 1 : 4;
-  auto kern = w == 1 ? (a.head_dim <= 32 ? tree_attn_f32<8, 1> : a.head_dim <= 64 ? tree_attn_f32<16, 1> : tree_attn_f32<32, 1>)
-                     : (a.head_dim <= 32 ? tree_attn_f32<8, 4> : a.head_dim <= 64 ? tree_attn_f32<16, 4> : tree_attn_f32<32, 4>);
+  const int w = longest > kF32Short ? 4 : a.head_dim > 64 && longest > kF32Short / 2 ? 2 : 1;
+  auto kern = a.head_dim <= 32   ? (w == 1 ? tree_attn_f32<8, 1> : tree_attn_f32<8, 4>)
+              : a.head_dim <= 64 ? (w == 1 ? tree_attn_f32<16, 1> : tree_attn_f32<16, 4>)
+                                 : (w == 1 ? tree_attn_f32<32, 1> : w == 2 ? tree_attn_f32<32, 2> : tree_attn_f32<32, 4>);
   hipLaunchKernelGGL(kern, dim3(a.n_q, node_count), dim3(64 * w), 0, st, a, node_begin);
   return hipGetLastError();
 }

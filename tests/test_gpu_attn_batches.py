@@ -78,10 +78,11 @@ def test_fp32_overflowed_scores(torch_cuda, head_dim):  # noqa: F811
     assert close(got.reshape(ref.shape), ref, "fp32") <= 0
 
 
-@pytest.mark.parametrize("longest", [0, 16, 17, 65])
+@pytest.mark.parametrize("longest", [0, 8, 9, 16, 17, 65])
 @pytest.mark.parametrize("head_dim", [4, 32, 36, 64, 96, 128])
 def test_fp32_short_contexts(torch_cuda, head_dim, longest):  # noqa: F811
-    """One wave a block up to 16 committed keys, four beyond; root paths of up to 16 nodes."""
+    """One wave a block up to 16 committed keys (two past 8 of more than 64 columns), four beyond; root paths of up to
+    16 nodes."""
     cfg = edge_cfg(dtype="fp32", B=4, n_q=6, n_kv=2, head_dim=head_dim, hidden=32, vocab=256, n_heads=15, topk=(2,) * 15)
     rng = np.random.default_rng(head_dim)
     trees = [synth.chain_tree(16), synth.random_tree(rng, 128), synth.chain_tree(1), synth.t16()]
