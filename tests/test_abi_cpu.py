@@ -352,7 +352,19 @@ def test_copied_mirrors_have_their_own_addresses():
 
 def test_resized_and_unwritable_mirrors_are_followed():
     """A mirror may be resized in place, put in the object's dict, read-only, strided or empty."""
-    pool = sm.KVPool(np.zeros((1, 8, 128), np.float32), FAKE, FAKE, [0], [8], [3])
+    import torch
+    for dev in (FAKE, torch.zeros(4)):                       # through the general form, and through the tensors' one
+        check_mirrors(sm.KVPool(torch.zeros(1, 8, 128), dev, dev, [0], [8], [3]))
+        trees = sm.Trees([0, 2], [-1, 0], [0, 1], [0, 0], dev_arrays=[dev] * 4)
+        want = dev if dev is FAKE else dev.data_ptr()
+        for mirror in (trees.rank_h, trees.rank_h.copy(), np.arange(4, dtype=np.int32)[::2]):
+            trees.rank_h = mirror
+            s = trees.struct()
+            assert (s.B, s.rank, s.node_off) == (1, want, want) and s.rank_h == mirror.ctypes.data
+            assert [s.node_off_h, s.parent_h, s.depth_h] == [a.ctypes.data for a in (trees.node_off_h, trees.parent_h, trees.depth_h)]
+
+
+def check_mirrors(pool):
     pool.struct()
     for _ in range(4):
         pool.seq_len_h.resize(100_000, refcheck=False)       # realloc moves it
